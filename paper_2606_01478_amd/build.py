@@ -17,6 +17,9 @@ import subprocess
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 SOURCES = ["cf_api.hip", "cf_step.hip", "cf_rollout.hip", "cf_rollout_bwd.hip", "cf_mppi.hip", "cf_probe.hip"]
+# sources compiled in several parts (-DCF_PART=i: a subset of the kernel variants
+# each), which run in parallel; the adjoint's variants alone take minutes
+PARTS = {"cf_step.hip": 3, "cf_rollout.hip": 3, "cf_rollout_bwd.hip": 4, "cf_mppi.hip": 2}
 # host-only runtime pieces (no device code), compiled by the host compiler
 HOST_SOURCES = ["cf_host.cpp"]
 HOST_FLAGS = ["-O2", "-std=c++17", "-fPIC", "-Wall", "-Wextra", "-I", os.path.join(ROOT, "include")]
@@ -59,11 +62,11 @@ def build(verbose: bool = False, extra_flags=(), incremental: bool = False) -> s
     bdir = os.path.join(ROOT, "_build")
     os.makedirs(bdir, exist_ok=True)
 
-    def compile_one(src):
-        obj = os.path.join(bdir, src.replace(".hip", ".o"))
+    def compile_one(src, part):
+        obj = os.path.join(bdir, src.replace(".hip", f".{part}.o"))
         if incremental and not extra_flags and not _stale(obj, os.path.join(HERE, "csrc", src)):
             return obj
-        cmd = [cc, *FLAGS, *extra_flags, "-c", os.path.join(HERE, "csrc", src), "-o", obj]
+        cmd = [cc, *FLAGS, *extra_flags, f"-DCF_PART={part}", "-c", os.path.join(HERE, "csrc", src), "-o", obj]
         if verbose:
             print(" ".join(cmd), flush=True)
         r = subprocess.run(cmd, capture_output=True, text=True)
@@ -83,8 +86,10 @@ def build(verbose: bool = False, extra_flags=(), incremental: bool = False) -> s
             raise RuntimeError(f"host compiler failed on {src}:\n{r.stderr}")
         return obj
 
-    with concurrent.futures.ThreadPoolExecutor(max_workers=len(SOURCES) + len(HOST_SOURCES)) as ex:
-        futs = [ex.submit(compile_one, s) for s in SOURCES] + [ex.submit(compile_host, s) for s in HOST_SOURCES]
+    with concurrent.futures.ThreadPoolExecutor(max_workers=min(8, os.cpu_count() or 8)) as ex:
+        units = [(s, i) for s in SOURCES for i in range(PARTS.get(s, 1))]
+        units.sort(key=lambda u: not u[0].startswith("cf_rollout"))   # the longest first
+        futs = [ex.submit(compile_one, *u) for u in units] + [ex.submit(compile_host, s) for s in HOST_SOURCES]
         objs = [f.result() for f in futs]
     tmp = LIB + ".tmp"
     cmd = [cc, f"--offload-arch={ARCH}", "-shared", "-o", tmp, *objs]

@@ -643,9 +643,14 @@ cf_status cf_create(const cf_desc* d, cf_handle** out) {
     hipError_t e;
     const size_t M = (size_t)h->M;
     std::vector<float> aos((size_t)NREC * M), soa((size_t)NREC * M);
-    for (size_t w = 0; w < M; ++w) cfh::derive_record(d->params + w * CF_NPARAM, aos.data() + w * NREC);
-    for (size_t w = 0; w < M; ++w)
-        for (int i = 0; i < NREC; ++i) soa[(size_t)i * M + w] = aos[w * NREC + i];
+    for (size_t w = 0; w < M; ++w) {
+        cfh::derive_record(d->params + w * CF_NPARAM, aos.data() + w * NREC);
+        cfh::derive_step(models[w], h->dt, aos.data() + w * NREC);
+    }
+    // transposed in blocks of worlds, so that both copies stay in cache
+    for (size_t w0 = 0; w0 < M; w0 += 64)
+        for (int i = 0; i < NREC; ++i)
+            for (size_t w = w0; w < std::min(M, w0 + 64); ++w) soa[(size_t)i * M + w] = aos[w * NREC + i];
     std::vector<int32_t> dw((size_t)std::max<int64_t>(D, 1));
     for (int w = 0; w < h->M; ++w)
         for (int64_t k = h->offsets[w]; k < h->offsets[w + 1]; ++k) dw[k] = w;

@@ -142,6 +142,75 @@ void derive_record(const float* r, float* out) {
     }
 }
 
+void derive_step(int model, float dt, float* out) {
+    const double h = dt;
+    std::fill(out + D_STEP, out + NREC, 0.f);
+    auto put = [&](int i, double v) { out[i] = (float)v; };
+    // stage values and update of W' = -c (W - W_cmd) over a step, as factors of the
+    // start deviation (z = c h)
+    auto lag = [&](double z, double* c) {
+        c[0] = 1.0;
+        c[1] = 1.0 - z / 2;
+        c[2] = 1.0 - z / 2 + z * z / 4;
+        c[3] = 1.0 - z + z * z / 2 - z * z * z / 4;
+        c[4] = 1.0 - z + z * z / 2 - z * z * z / 6 + z * z * z * z / 24;
+    };
+    double c[5];
+    if (model == MODEL_FP) {
+        // twice the specific thrust, torques over inertia, per rotor thrust difference
+        const double m = out[P_MASS], s = 2.0 / m;
+        put(F_K1, s * out[D_K1W]);
+        put(F_K2, s * out[P_THRUST + 2]);
+        put(F_A2R, s * out[D_F4R]);
+        const int mix[3] = {P_MIX_TX, P_MIX_TY, D_TZK}, to[3] = {F_TX, F_TY, F_TZ}, base[3] = {D_TXR, D_TYR, D_TZR};
+        for (int a = 0; a < 3; ++a) {
+            const double J = out[P_J + a];
+            for (int i = 0; i < 4; ++i) put(to[a] + i, out[mix[a] + i] / (s * J));
+            put(F_TR + a, out[base[a]] / J);
+        }
+        const double Jx = out[P_J], Jy = out[P_J + 1], Jz = out[P_J + 2];
+        put(F_DJ, (Jz - Jy) / Jx);
+        put(F_DJ + 1, (Jx - Jz) / Jy);
+        put(F_DJ + 2, (Jy - Jx) / Jz);
+        const double z = (double)out[P_MOTOR_UP] * h;
+        lag(z, c);
+        put(F_P2, c[1]);
+        put(F_P4, c[3]);
+        put(F_PF, c[4]);
+        put(F_Q2, z / 2);
+        put(F_Q4, z - z * z / 2 + z * z * z / 4);
+        put(F_QF, z - z * z / 2 + z * z * z / 6 - z * z * z * z / 24);
+        // the wrench is quadratic in the stage factor, so its value at stage 3 follows
+        // from stages 1, 2 and 4 (Lagrange weights, common factors of z cancelled)
+        const double a = 0.5 - z / 4 + z * z / 4, b = 1.0 - z / 2 + z * z / 4, d = 0.5 - z / 2 + z * z / 4;
+        const double l1 = (z / 2) * a / b, l4 = -(z / 4) * (0.5 - z / 4) / (b * d);
+        put(F_L1, l1);
+        put(F_L4, l4);
+        put(F_L2, 1.0 - l1 - l4);
+        return;
+    }
+    for (int i = 0; i < 3; ++i) {
+        // RK4 of the linear attitude response Psi'' = c1 Psi + c2 Psi' + c3 Psi_cmd is its
+        // Taylor polynomial of order 4, in terms of Psi' and Psi'' at the start
+        const double c1 = out[P_CPSI1 + i], c2 = out[P_CPSI2 + i], c12 = c1 * c2, cc = c1 + c2 * c2;
+        const double h2 = h * h / 2, h3 = h * h * h / 6, h4 = h * h * h * h / 24;
+        put(I_AL + i, h + h3 * c1 + h4 * c12);
+        put(I_BE + i, h2 + h3 * c2 + h4 * cc);
+        put(I_GA + i, h2 * c1 + h3 * c12 + h4 * c1 * cc);
+        put(I_DE + i, h + h2 * c2 + h3 * cc + h4 * (c12 + c2 * cc));
+        put(I_A4 + i, h + h * h * h / 4 * c1);
+        put(I_B4 + i, h2 + h * h * h / 4 * c2);
+    }
+    const double ct = out[P_CTAU];
+    lag(ct * h, c);
+    // without thrust dynamics (c_tau = 0) the commanded thrust acts at every stage
+    for (int s = 0; s < 5; ++s) {
+        const double f = ct == 0.0 ? 0.0 : c[s];
+        put(s < 4 ? I_P + s : I_PF, f);
+        put(s < 4 ? I_Q + s : I_QF, 1.0 - f);
+    }
+}
+
 namespace {
 int model_cost(int model, int ctrl) {
     if (model == MODEL_ID) return 2;

@@ -28,6 +28,10 @@ cf_status validate_desc(const cf_desc* d, std::vector<int32_t>& counts, std::vec
 // thrust of the identified model).
 void derive_record(const float* r, float* out);
 
+// out[D_STEP..NREC): the coefficients of an RK4 step of length dt of a world of
+// `model`, from the record out[0..D_STEP) that derive_record formed.
+void derive_step(int model, float dt, float* out);
+
 // True when the rotor drag-torque polynomial is the thrust polynomial times one
 // constant kappa (t_j = kappa k_j for j = 0, 1, 2, to 2^-20 relative); *kappa
 // receives it. The reduced kernel variants then form the yaw torque from the

@@ -24,7 +24,23 @@ enum : int {
     D_INV_M = 96, D_IJ = 97, D_DJ = 100, D_INV_2K2 = 103, D_SG = 104, D_WR = 108, D_W2 = 109,
     D_K1W = 110, D_T1W = 111, D_FR = 112, D_F4R = 113, D_TXR = 114, D_TYR = 115, D_TZR = 116,
     D_SGR = 117, D_DISC_R = 118, D_VTX = 119, D_CF_M = 120, D_F_HOVER = 121, D_TPROP = 122, D_TZK = 123,
-    NREC = 128
+    D_STEP = 128,   // coefficients of the step (below), which depend on dt and the world's model
+    NREC = 160
+};
+// Coefficients of one RK4 step of length dt that follow from a world's record
+// alone (see the structured steps in cf_device.hpp), formed in binary64 on the
+// host. First-principles worlds: the scaled thrust and mixing terms and the
+// linear rotor law's polynomials; identified worlds: the attitude and thrust
+// responses, which are linear.
+enum : int {
+    F_K1 = D_STEP, F_K2 = D_STEP + 1, F_A2R = D_STEP + 2, F_TX = D_STEP + 3, F_TY = D_STEP + 7, F_TZ = D_STEP + 11,
+    F_TR = D_STEP + 15, F_DJ = D_STEP + 18, F_P2 = D_STEP + 21, F_P4 = D_STEP + 22, F_PF = D_STEP + 23,
+    F_Q2 = D_STEP + 24, F_Q4 = D_STEP + 25, F_QF = D_STEP + 26, F_L1 = D_STEP + 27, F_L2 = D_STEP + 28,
+    F_L4 = D_STEP + 29
+};
+enum : int {
+    I_AL = D_STEP, I_BE = D_STEP + 3, I_GA = D_STEP + 6, I_DE = D_STEP + 9, I_A4 = D_STEP + 12, I_B4 = D_STEP + 15,
+    I_P = D_STEP + 18, I_PF = D_STEP + 22, I_Q = D_STEP + 23, I_QF = D_STEP + 27
 };
 enum : int { MODEL_FP = 0, MODEL_ID = 1 };
 enum : int { CTRL_ROTOR = 0, CTRL_PID = 1, CTRL_TORQUE = 2, CTRL_POSITION = 3 };

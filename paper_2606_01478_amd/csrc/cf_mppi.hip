@@ -6,9 +6,12 @@
 // over (cost, sample index), regenerates the elites' commands from their
 // counters and forms the exponentially weighted mean in a fixed order.
 #include "cf_device.hpp"
+#include "cf_dispatch.hpp"
 #include "cf_internal.hpp"
 
 namespace cfk {
+
+constexpr int MPPI_PARTS = 2;
 
 // ---- Philox4x64-10 (Salmon, Moraes, Dror, Shaw, SC'11) ------------------------
 constexpr uint64_t PH_M0 = 0xD2E7470EE14C6C93ull, PH_M1 = 0xCA5A826395121157ull;
@@ -153,6 +156,7 @@ __global__ __launch_bounds__(256) void k_mppi_rollout(MppiArgs a) {
     a.cost[(size_t)c * a.N + k] = isfinite(J) ? J : __builtin_inff();
 }
 
+#if CF_PART == 0
 // correlated noise only (eps, before sigma and clipping), [C][N][H][4]
 __global__ __launch_bounds__(256) void k_mppi_noise(MppiArgs a) {
     const int c = blockIdx.y;
@@ -413,6 +417,8 @@ __global__ void k_mppi_pick(MppiArgs a) {
         for (int j = 0; j < 4; ++j) a.u_apply[j] = a.mean_out[(size_t)b * a.H * 4 + j];
 }
 
+#endif  // CF_PART == 0
+
 template <int MODEL, int CTRL, int INTEG, bool AERO>
 static hipError_t launch_roll(const KernelSel&, const MppiArgs& a, hipStream_t s) {
     const dim3 grid((unsigned)((a.N + 255) / 256), (unsigned)a.C);
@@ -426,30 +432,22 @@ static hipError_t launch_roll(const KernelSel&, const MppiArgs& a, hipStream_t s
     return hipGetLastError();
 }
 
-#define CF_MPPI_DISPATCH_A(A)                                                                \
-    switch (ks.models * 8 + ks.ctrl * 2 + ks.integ) {                                        \
-        case MS_FP * 8 + 0: return launch_roll<MODEL_FP, CTRL_ROTOR, EULER, A>(ks, a, s);    \
-        case MS_FP * 8 + 1: return launch_roll<MODEL_FP, CTRL_ROTOR, RK4, A>(ks, a, s);      \
-        case MS_FP * 8 + 2: return launch_roll<MODEL_FP, CTRL_PID, EULER, A>(ks, a, s);      \
-        case MS_FP * 8 + 3: return launch_roll<MODEL_FP, CTRL_PID, RK4, A>(ks, a, s);        \
-        case MS_FP * 8 + 4: return launch_roll<MODEL_FP, CTRL_TORQUE, EULER, A>(ks, a, s);   \
-        case MS_FP * 8 + 5: return launch_roll<MODEL_FP, CTRL_TORQUE, RK4, A>(ks, a, s);     \
-        case MS_FP * 8 + 6: return launch_roll<MODEL_FP, CTRL_POSITION, EULER, A>(ks, a, s); \
-        case MS_FP * 8 + 7: return launch_roll<MODEL_FP, CTRL_POSITION, RK4, A>(ks, a, s);   \
-        case MS_ID * 8 + 0: case MS_ID * 8 + 2: case MS_ID * 8 + 4: case MS_ID * 8 + 6:      \
-            return launch_roll<MODEL_ID, CTRL_ROTOR, EULER, A>(ks, a, s);                    \
-        case MS_ID * 8 + 1: case MS_ID * 8 + 3: case MS_ID * 8 + 5: case MS_ID * 8 + 7:      \
-            return launch_roll<MODEL_ID, CTRL_ROTOR, RK4, A>(ks, a, s);                      \
-        default: break;                                                                      \
-    }
+template <int P>
+hipError_t launch_mppi_part(const KernelSel& ks, const MppiArgs& a, hipStream_t s);
+
+template <>
+hipError_t launch_mppi_part<CF_PART>(const KernelSel& ks, const MppiArgs& a, hipStream_t s) {
+    return dispatch<MPPI_PARTS>(ks, [&](auto m, auto c, auto i, auto e) {
+        if constexpr (m() == MS_BOTH) return hipErrorInvalidValue;   // one world
+        else return launch_roll<m() == MS_FP ? MODEL_FP : MODEL_ID, c(), i(), e() != 0>(ks, a, s);
+    });
+}
+
+#if CF_PART == 0
+template <> hipError_t launch_mppi_part<1>(const KernelSel&, const MppiArgs&, hipStream_t);
 
 hipError_t launch_mppi_rollout(const KernelSel& ks, const MppiArgs& a, hipStream_t s) {
-    if (ks.aero) {
-        CF_MPPI_DISPATCH_A(true)
-    } else {
-        CF_MPPI_DISPATCH_A(false)
-    }
-    return hipErrorInvalidValue;
+    return in_part<MPPI_PARTS>(ks, [&](auto p) { return launch_mppi_part<p()>(ks, a, s); });
 }
 
 hipError_t launch_mppi_noise(const MppiArgs& a, hipStream_t s) {
@@ -465,5 +463,7 @@ hipError_t launch_mppi_select(const MppiArgs& a, hipStream_t s) {
     hipLaunchKernelGGL(k_mppi_pick, dim3(1), dim3(64), 0, s, a);
     return hipGetLastError();
 }
+
+#endif
 
 }  // namespace cfk

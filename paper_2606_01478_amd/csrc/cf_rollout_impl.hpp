@@ -16,6 +16,7 @@
 #include <type_traits>
 
 #include "cf_device.hpp"
+#include "cf_dispatch.hpp"
 #include "cf_internal.hpp"
 
 namespace cfk {
@@ -1036,36 +1037,5 @@ static hipError_t launch_bwd_t(const KernelSel& ks, const RollArgs& a, const int
                                hipStream_t s) {
     return launch_roll_t<true, MODELS, CTRL, INTEG, AERO>(ks, a, tiles, n_tiles, s);
 }
-
-#define CF_DISPATCH_A(FN, A, ...)                                                       \
-    switch (ks.models * 8 + ks.ctrl * 2 + ks.integ) {                                   \
-        case MS_FP * 8 + 0: return FN<MS_FP, CTRL_ROTOR, EULER, A>(__VA_ARGS__);        \
-        case MS_FP * 8 + 1: return FN<MS_FP, CTRL_ROTOR, RK4, A>(__VA_ARGS__);          \
-        case MS_FP * 8 + 2: return FN<MS_FP, CTRL_PID, EULER, A>(__VA_ARGS__);          \
-        case MS_FP * 8 + 3: return FN<MS_FP, CTRL_PID, RK4, A>(__VA_ARGS__);            \
-        case MS_FP * 8 + 4: return FN<MS_FP, CTRL_TORQUE, EULER, A>(__VA_ARGS__);       \
-        case MS_FP * 8 + 5: return FN<MS_FP, CTRL_TORQUE, RK4, A>(__VA_ARGS__);         \
-        case MS_FP * 8 + 6: return FN<MS_FP, CTRL_POSITION, EULER, A>(__VA_ARGS__);     \
-        case MS_FP * 8 + 7: return FN<MS_FP, CTRL_POSITION, RK4, A>(__VA_ARGS__);       \
-        case MS_ID * 8 + 0: case MS_ID * 8 + 2: case MS_ID * 8 + 4: case MS_ID * 8 + 6: \
-            return FN<MS_ID, CTRL_ROTOR, EULER, A>(__VA_ARGS__);                        \
-        case MS_ID * 8 + 1: case MS_ID * 8 + 3: case MS_ID * 8 + 5: case MS_ID * 8 + 7: \
-            return FN<MS_ID, CTRL_ROTOR, RK4, A>(__VA_ARGS__);                          \
-        case MS_BOTH * 8 + 0: return FN<MS_BOTH, CTRL_ROTOR, EULER, A>(__VA_ARGS__);    \
-        case MS_BOTH * 8 + 1: return FN<MS_BOTH, CTRL_ROTOR, RK4, A>(__VA_ARGS__);      \
-        case MS_BOTH * 8 + 2: return FN<MS_BOTH, CTRL_PID, EULER, A>(__VA_ARGS__);      \
-        case MS_BOTH * 8 + 3: return FN<MS_BOTH, CTRL_PID, RK4, A>(__VA_ARGS__);        \
-        case MS_BOTH * 8 + 4: return FN<MS_BOTH, CTRL_TORQUE, EULER, A>(__VA_ARGS__);   \
-        case MS_BOTH * 8 + 5: return FN<MS_BOTH, CTRL_TORQUE, RK4, A>(__VA_ARGS__);     \
-        case MS_BOTH * 8 + 6: return FN<MS_BOTH, CTRL_POSITION, EULER, A>(__VA_ARGS__); \
-        case MS_BOTH * 8 + 7: return FN<MS_BOTH, CTRL_POSITION, RK4, A>(__VA_ARGS__);   \
-        default: break;                                                                 \
-    }
-#define CF_DISPATCH(FN, ...)                                                             \
-    if (ks.aero) {                                                                       \
-        CF_DISPATCH_A(FN, true, __VA_ARGS__)                                             \
-    } else {                                                                             \
-        CF_DISPATCH_A(FN, false, __VA_ARGS__)                                            \
-    }
 
 }  // namespace cfk

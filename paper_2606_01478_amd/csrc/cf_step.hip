@@ -2,9 +2,12 @@
 // registers (K = 1 is the plain single-step kernel), in three lane mappings
 // (per-lane world, one world per tile, persistent work queue over tiles).
 #include "cf_device.hpp"
+#include "cf_dispatch.hpp"
 #include "cf_internal.hpp"
 
 namespace cfk {
+
+constexpr int STEP_PARTS = 3;
 
 // One drone, K steps with a held command; state rows st[i*D + d].
 // MR: variant for an onboard controller slower than the physics
@@ -187,46 +190,45 @@ static int wq_blocks_t(int tile) {
     return nb > 0 ? nb : 1;
 }
 
-#define CF_DISPATCH_A(FN, A, ...)                                                       \
-    switch (ks.models * 8 + ks.ctrl * 2 + ks.integ) {                                   \
-        case MS_FP * 8 + 0: return FN<MS_FP, CTRL_ROTOR, EULER, A>(__VA_ARGS__);        \
-        case MS_FP * 8 + 1: return FN<MS_FP, CTRL_ROTOR, RK4, A>(__VA_ARGS__);          \
-        case MS_FP * 8 + 2: return FN<MS_FP, CTRL_PID, EULER, A>(__VA_ARGS__);          \
-        case MS_FP * 8 + 3: return FN<MS_FP, CTRL_PID, RK4, A>(__VA_ARGS__);            \
-        case MS_FP * 8 + 4: return FN<MS_FP, CTRL_TORQUE, EULER, A>(__VA_ARGS__);       \
-        case MS_FP * 8 + 5: return FN<MS_FP, CTRL_TORQUE, RK4, A>(__VA_ARGS__);         \
-        case MS_FP * 8 + 6: return FN<MS_FP, CTRL_POSITION, EULER, A>(__VA_ARGS__);     \
-        case MS_FP * 8 + 7: return FN<MS_FP, CTRL_POSITION, RK4, A>(__VA_ARGS__);       \
-        case MS_ID * 8 + 0: case MS_ID * 8 + 2: case MS_ID * 8 + 4: case MS_ID * 8 + 6: \
-            return FN<MS_ID, CTRL_ROTOR, EULER, A>(__VA_ARGS__);                        \
-        case MS_ID * 8 + 1: case MS_ID * 8 + 3: case MS_ID * 8 + 5: case MS_ID * 8 + 7: \
-            return FN<MS_ID, CTRL_ROTOR, RK4, A>(__VA_ARGS__);                          \
-        case MS_BOTH * 8 + 0: return FN<MS_BOTH, CTRL_ROTOR, EULER, A>(__VA_ARGS__);    \
-        case MS_BOTH * 8 + 1: return FN<MS_BOTH, CTRL_ROTOR, RK4, A>(__VA_ARGS__);      \
-        case MS_BOTH * 8 + 2: return FN<MS_BOTH, CTRL_PID, EULER, A>(__VA_ARGS__);      \
-        case MS_BOTH * 8 + 3: return FN<MS_BOTH, CTRL_PID, RK4, A>(__VA_ARGS__);        \
-        case MS_BOTH * 8 + 4: return FN<MS_BOTH, CTRL_TORQUE, EULER, A>(__VA_ARGS__);   \
-        case MS_BOTH * 8 + 5: return FN<MS_BOTH, CTRL_TORQUE, RK4, A>(__VA_ARGS__);     \
-        case MS_BOTH * 8 + 6: return FN<MS_BOTH, CTRL_POSITION, EULER, A>(__VA_ARGS__); \
-        case MS_BOTH * 8 + 7: return FN<MS_BOTH, CTRL_POSITION, RK4, A>(__VA_ARGS__);   \
-        default: break;                                                                 \
-    }
-#define CF_DISPATCH(FN, ...)                                                             \
-    if (ks.aero) {                                                                       \
-        CF_DISPATCH_A(FN, true, __VA_ARGS__)                                             \
-    } else {                                                                             \
-        CF_DISPATCH_A(FN, false, __VA_ARGS__)                                            \
-    }
+// the launches and occupancies of the variants compiled in part P (cf_dispatch.hpp)
+template <int P>
+hipError_t launch_step_part(const KernelSel& ks, const StepArgs& a, const int4* tiles, int n_tiles, unsigned* counter,
+                            int wq_blocks, hipStream_t s);
+template <int P>
+int step_wq_part(const KernelSel& ks);
 
-hipError_t launch_step(const KernelSel& ks, const StepArgs& a, const int4* tiles, int n_tiles,
-                       unsigned* counter, int wq_blocks, hipStream_t s) {
-    CF_DISPATCH(launch_step_t, ks, a, tiles, n_tiles, counter, wq_blocks, s)
-    return hipErrorInvalidValue;
+template <>
+hipError_t launch_step_part<CF_PART>(const KernelSel& ks, const StepArgs& a, const int4* tiles, int n_tiles,
+                                     unsigned* counter, int wq_blocks, hipStream_t s) {
+    return dispatch<STEP_PARTS>(ks, [&](auto m, auto c, auto i, auto e) {
+        return launch_step_t<m(), c(), i(), e() != 0>(ks, a, tiles, n_tiles, counter, wq_blocks, s);
+    });
+}
+
+template <>
+int step_wq_part<CF_PART>(const KernelSel& ks) {
+    int n = 1;
+    (void)dispatch<STEP_PARTS>(ks, [&](auto m, auto c, auto i, auto e) {
+        n = wq_blocks_t<m(), c(), i(), e() != 0>(ks.tile);
+        return hipSuccess;
+    });
+    return n;
+}
+
+#if CF_PART == 0
+template <> hipError_t launch_step_part<1>(const KernelSel&, const StepArgs&, const int4*, int, unsigned*, int, hipStream_t);
+template <> hipError_t launch_step_part<2>(const KernelSel&, const StepArgs&, const int4*, int, unsigned*, int, hipStream_t);
+template <> int step_wq_part<1>(const KernelSel&);
+template <> int step_wq_part<2>(const KernelSel&);
+
+hipError_t launch_step(const KernelSel& ks, const StepArgs& a, const int4* tiles, int n_tiles, unsigned* counter,
+                       int wq_blocks, hipStream_t s) {
+    return in_part<STEP_PARTS>(ks, [&](auto p) { return launch_step_part<p()>(ks, a, tiles, n_tiles, counter, wq_blocks, s); });
 }
 
 int step_wq_blocks_per_cu(const KernelSel& ks) {
-    CF_DISPATCH(wq_blocks_t, ks.tile)
-    return 1;
+    return in_part<STEP_PARTS>(ks, [&](auto p) { return step_wq_part<p()>(ks); });
 }
+#endif
 
 }  // namespace cfk

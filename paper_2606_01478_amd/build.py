@@ -16,7 +16,8 @@ import subprocess
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
-SOURCES = ["cf_api.hip", "cf_step.hip", "cf_rollout.hip", "cf_rollout_bwd.hip", "cf_mppi.hip", "cf_probe.hip"]
+SOURCES = ["cf_api.hip", "cf_step.hip", "cf_rollout.hip", "cf_rollout_bwd.hip", "cf_quad.hip", "cf_mppi.hip",
+           "cf_probe.hip"]
 # sources compiled in several parts (-DCF_PART=i: a subset of the kernel variants
 # each), which run in parallel; the adjoint's variants alone take minutes
 PARTS = {"cf_step.hip": 3, "cf_rollout.hip": 3, "cf_rollout_bwd.hip": 4, "cf_mppi.hip": 2}

@@ -11,6 +11,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <map>
+#include <memory>
 #include <mutex>
 #include <new>
 #include <string>
@@ -502,6 +503,38 @@ KernelSel selection(const cf_handle* h, int mode, int tile) {
     return ks;
 }
 
+// Whether the handle's kernels can put a drone on four lanes (cf_quad.hpp): one model
+// in its reduced variant under RK4, the rotor or attitude interface with the
+// controller on every step; and whether its drones are few enough, `per_cu` for each
+// compute unit, that one lane each would leave SIMDs idle.
+bool quad_ok(const cf_handle* h, int per_cu) {
+    const bool fp = h->models == MS_FP;
+    return h->lane_ok && !h->aero && h->integ == CF_INTEG_RK4 && h->ctrl_every == 1 &&
+           (!fp || h->control == CF_CTRL_ROTOR || h->control == CF_CTRL_ATT_PID) && h->D > 0 &&
+           h->D <= (int64_t)h->cus * per_cu;
+}
+
+// lane mapping of a held-step launch of K steps
+int held_mode(const cf_handle* h, int K) {
+    if (h->use_wq) return LM_WQ;
+    const bool pid = h->models == MS_FP && h->control == CF_CTRL_ATT_PID;
+    return quad_ok(h, K == 1 ? QUAD_HELD_ONE : (pid ? QUAD_HELD_PID : QUAD_HELD)) ? LM_QUAD : h->mode;
+}
+
+// steps of one launch of a k-step call
+int held_chunk(const cf_handle* h, int k) {
+    const int n = h->ctrl_every;   // k is a multiple of n: every launch starts on a controller step
+    if (h->flags & CF_F_PLAIN_KERNEL) return n;
+    const int chunk = (h->chunk > 0 && h->chunk < k) ? h->chunk : k;
+    return ((chunk + n - 1) / n) * n;
+}
+
+// the packed tiles of the current tile size, where a k-step call's launches use them
+hipError_t tiles_for_steps(cf_handle* h, int k) {
+    const int mode = held_mode(h, held_chunk(h, k));
+    return mode == LM_TILE || mode == LM_WQ ? build_packed_tiles(h, h->tile) : hipSuccess;
+}
+
 StepArgs step_args(const cf_handle* h, float* st, const float* cmd, int K, uint32_t* nf) {
     StepArgs a;
     a.st = st;
@@ -642,20 +675,24 @@ cf_status cf_create(const cf_desc* d, cf_handle** out) {
     };
     hipError_t e;
     const size_t M = (size_t)h->M;
-    std::vector<float> aos((size_t)NREC * M), soa((size_t)NREC * M);
+    std::unique_ptr<float[]> aos(new (std::nothrow) float[(size_t)NREC * M]);
+    // the transposed copy serves worlds of a handful of drones, one per lane
+    const bool lanes = h->lane_ok && (double)D / h->M < 32.0;
+    std::unique_ptr<float[]> soa(lanes ? new (std::nothrow) float[(size_t)NREC * M] : nullptr);
+    if (!aos || (lanes && !soa)) return fail(hipErrorOutOfMemory);
     for (size_t w = 0; w < M; ++w) {
-        cfh::derive_record(d->params + w * CF_NPARAM, aos.data() + w * NREC);
-        cfh::derive_step(models[w], h->dt, aos.data() + w * NREC);
+        cfh::derive_record(d->params + w * CF_NPARAM, aos.get() + w * NREC);
+        cfh::derive_step(models[w], h->dt, aos.get() + w * NREC);
     }
     // transposed in blocks of worlds, so that both copies stay in cache
-    for (size_t w0 = 0; w0 < M; w0 += 64)
+    for (size_t w0 = 0; lanes && w0 < M; w0 += 64)
         for (int i = 0; i < NREC; ++i)
             for (size_t w = w0; w < std::min(M, w0 + 64); ++w) soa[(size_t)i * M + w] = aos[w * NREC + i];
     std::vector<int32_t> dw((size_t)std::max<int64_t>(D, 1));
     for (int w = 0; w < h->M; ++w)
         for (int64_t k = h->offsets[w]; k < h->offsets[w + 1]; ++k) dw[k] = w;
     if ((e = dalloc(&h->par_aos, M * NREC)) != hipSuccess) return fail(e);
-    if ((e = dalloc(&h->par_soa, M * NREC)) != hipSuccess) return fail(e);
+    if (lanes && (e = dalloc(&h->par_soa, M * NREC)) != hipSuccess) return fail(e);
     if ((e = dalloc(&h->drone_world, (size_t)std::max<int64_t>(D, 1))) != hipSuccess) return fail(e);
     if ((e = dalloc(&h->d_offsets, M + 1)) != hipSuccess) return fail(e);
     if ((e = dalloc(&h->d_gidx, M)) != hipSuccess) return fail(e);
@@ -666,10 +703,9 @@ cf_status cf_create(const cf_desc* d, cf_handle** out) {
     if ((e = hipMemset(h->dflag, 0, sizeof(uint32_t))) != hipSuccess) return fail(e);
     h->n_counters = 4096;
     if ((e = dalloc(&h->counters, (size_t)h->n_counters)) != hipSuccess) return fail(e);
-    if ((e = hipMemcpy(h->par_aos, aos.data(), aos.size() * sizeof(float), hipMemcpyHostToDevice)) != hipSuccess)
-        return fail(e);
-    if ((e = hipMemcpy(h->par_soa, soa.data(), soa.size() * sizeof(float), hipMemcpyHostToDevice)) != hipSuccess)
-        return fail(e);
+    const size_t rec_bytes = (size_t)NREC * M * sizeof(float);
+    if ((e = hipMemcpy(h->par_aos, aos.get(), rec_bytes, hipMemcpyHostToDevice)) != hipSuccess) return fail(e);
+    if (lanes && (e = hipMemcpy(h->par_soa, soa.get(), rec_bytes, hipMemcpyHostToDevice)) != hipSuccess) return fail(e);
     if ((e = hipMemcpy(h->drone_world, dw.data(), dw.size() * sizeof(int32_t), hipMemcpyHostToDevice)) != hipSuccess)
         return fail(e);
     if ((e = hipMemcpy(h->d_offsets, h->offsets.data(), (M + 1) * sizeof(int64_t), hipMemcpyHostToDevice)) != hipSuccess)
@@ -858,14 +894,13 @@ static cf_status enqueue_steps(cf_handle* h, float* state, const float* cmd, int
         h->timers[0].n = 0;
         h->timers[1].n = 0;
     }
-    // the packed tiles of the current tile size (built before any graph capture
-    // by cf_step_k, so this returns at once there)
-    if ((e = build_packed_tiles(h, h->tile)) != hipSuccess) return note(h, e);
-    const int n = h->ctrl_every;  // k is a multiple of n: every launch starts on a controller step
+    // built before any graph capture by cf_step_k, so this returns at once there
+    if ((e = tiles_for_steps(h, k)) != hipSuccess) return note(h, e);
     if (plain) {
+        const int n = h->ctrl_every;
         // one step per launch; with a slower onboard controller, one controller
         // period per launch (its held commands are not part of the state)
-        const int mode = h->mode == LM_LANE ? LM_LANE : LM_TILE;
+        const int held = held_mode(h, n), mode = held == LM_WQ ? LM_TILE : held;
         const StepArgs a = step_args(h, state, cmd, n, nf);
         e = per_model_packed(h, s, h->split, only, [&](int models, const int4* tiles, int nt, hipStream_t st, int) {
             KernelSel ks = selection(h, mode, h->tile);
@@ -880,8 +915,7 @@ static cf_status enqueue_steps(cf_handle* h, float* state, const float* cmd, int
         });
         return note(h, e);
     }
-    int chunk = (h->chunk > 0 && h->chunk < k) ? h->chunk : k;
-    chunk = ((chunk + n - 1) / n) * n;
+    const int chunk = held_chunk(h, k);
     const int n_launch = (k + chunk - 1) / chunk;
     // queue heads: one per launch, the first-principles launches' in the first half
     // of the counter array, the identified ones' in the second (a model's graph
@@ -897,7 +931,7 @@ static cf_status enqueue_steps(cf_handle* h, float* state, const float* cmd, int
         }
     }
     e = per_model_packed(h, s, h->split, only, [&](int models, const int4* tiles, int nt, hipStream_t st, int slot) {
-        KernelSel ks = selection(h, h->use_wq ? LM_WQ : h->mode, h->tile);
+        KernelSel ks = selection(h, held_mode(h, chunk), h->tile);
         ks.models = models;
         int blocks = 0;
         if (h->use_wq) {
@@ -929,7 +963,7 @@ cf_status cf_step_k(cf_handle* h, float* state, const float* cmd, int32_t k, uin
         return CF_EINVAL;
     if (nf && check_dev(nf, (size_t)h->M * sizeof(uint32_t))) return CF_EINVAL;
     hipSetDevice(h->device);
-    hipError_t e = build_packed_tiles(h, h->tile);
+    hipError_t e = tiles_for_steps(h, k);
     if (e != hipSuccess) return note(h, e);
     const int plain = (h->flags & CF_F_PLAIN_KERNEL) ? 1 : 0;
     if (!(h->flags & CF_F_GRAPH)) return enqueue_steps(h, state, cmd, k, nf, h->stream, plain);
@@ -991,7 +1025,13 @@ cf_status cf_step_k(cf_handle* h, float* state, const float* cmd, int32_t k, uin
 // rollout
 
 static int roll_mode(const cf_handle* h) {
+    // LM_LANE or LM_TILE; quad_roll() overrides it
     return (h->lane_ok && h->D > 0 && (double)h->D / h->M < 32.0) ? LM_LANE : LM_TILE;
+}
+
+// rollouts on quads: the tracking objective on the figure-eight, linear feedback
+static bool quad_roll(const cf_handle* h, const RollArgs& a) {
+    return quad_ok(h, QUAD_ROLL) && a.obj_kind == 0 && !a.ref_user && !a.ref_shift && !a.squash && a.mlp_H == 0;
 }
 
 // ref_tab_buf: device [(T + 1)][6] for the figure-eight table, or null to use the
@@ -1160,11 +1200,13 @@ cf_status cf_rollout(cf_handle* h, const float* x0, const float* cmds, int32_t T
         a.loss = (float*)h->loss_tmp.p;
     }
     if (h->D > 0) {
+        const bool quad = quad_roll(h, a);
         const int mode = roll_mode(h);
-        if (mode == LM_TILE && (e = build_tiles(h, h->tile)) != hipSuccess) return note(h, e);
+        if (!quad && mode == LM_TILE && (e = build_tiles(h, h->tile)) != hipSuccess) return note(h, e);
         e = per_model(h, h->stream, h->split, [&](int models, const int4* tiles, int nt, hipStream_t st, int) {
             KernelSel ks = selection(h, mode, mode == LM_LANE ? 64 : h->tile);
             ks.models = models;
+            if (quad) return launch_rollout_quad(ks, a, false, st);
             return launch_rollout_fwd(ks, a, tiles, nt, st);
         });
         if (e != hipSuccess) return note(h, e);
@@ -1283,11 +1325,13 @@ static cf_status rollout_backward_impl(cf_handle* h, const float* cmds, int32_t 
     a.ggc = (g_gain && Hp == 0) ? sc.ggc : nullptr;
     a.mlp_rec = (g_gain && Hp > 0) ? sc.rec : nullptr;
     if (h->D > 0) {
+        const bool quad = quad_roll(h, a);
         const int mode = roll_mode(h);
-        if (mode == LM_TILE && (e = build_tiles(h, h->tile)) != hipSuccess) return note(h, e);
+        if (!quad && mode == LM_TILE && (e = build_tiles(h, h->tile)) != hipSuccess) return note(h, e);
         e = per_model(h, h->stream, h->split, [&](int models, const int4* tiles, int nt, hipStream_t st, int) {
             KernelSel ks = selection(h, mode, mode == LM_LANE ? 64 : h->tile);
             ks.models = models;
+            if (quad) return launch_rollout_quad(ks, a, true, st);
             return launch_rollout_bwd(ks, a, tiles, nt, st);
         });
         if (e != hipSuccess) return note(h, e);

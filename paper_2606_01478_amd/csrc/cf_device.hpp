@@ -65,9 +65,16 @@ __device__ __forceinline__ ScalarRec laundered(AosRec r) {
     asm volatile("" : "+s"(r.r));
     return ScalarRec{r.r};
 }
-__device__ __forceinline__ SoaRec laundered(SoaRec r) {
+// (a laundered pointer has no address space of its own: say that it is global)
+struct GlobalSoaRec {
+    const float* p; int M; int w;
+    __device__ __forceinline__ float operator()(int i) const {
+        return ((const __attribute__((address_space(1))) float*)p)[(size_t)i * M + w];
+    }
+};
+__device__ __forceinline__ GlobalSoaRec laundered(SoaRec r) {
     asm volatile("" : "+s"(r.p));
-    return r;
+    return GlobalSoaRec{r.p, r.M, r.w};
 }
 __device__ __forceinline__ ScalarRec laundered(ScalarRec r) {
     asm volatile("" : "+s"(r.r));
@@ -730,7 +737,8 @@ __device__ __forceinline__ void allocate(const float* wrench, const FpParams& P,
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
         const float dfr = fmaf(C.A[4 * j], wrench[0], -P.fr) +
-                          (C.A[4 * j + 1] * wrench[1] + C.A[4 * j + 2] * wrench[2] + C.A[4 * j + 3] * wrench[3]);
+                          __builtin_fmaf(C.A[4 * j + 3], wrench[3],
+                                         __builtin_fmaf(C.A[4 * j + 2], wrench[2], C.A[4 * j + 1] * wrench[1]));
         const float lo = -P.fr, hi = C.fmax - P.fr;
         const float df = fminf(fmaxf(dfr, lo), hi);
         const float disc = fmaf(4.f * P.k2, df, P.disc_r);
@@ -863,29 +871,32 @@ __device__ __forceinline__ void pos_vjp(const float* x, const PidParams& C, cons
 
 // x: 25-component state; u: [roll, pitch, yawrate, thrust]. Writes rotor
 // commands rc[4] and the new controller state cs[8] = [I_a(2), I_r(3), w_prev(3)].
+// Each multiply-add is written out: the quad kernels (cf_quad.hpp) repeat them, so
+// that a drone's states do not depend on which kernel the batch's size selects.
 __device__ __forceinline__ void pid_forward(const float* x, const float* u, const FpParams& P,
                                             const PidParams& C, float dt, float inv_dt,
                                             float* rc, float* cs, PidTrace& tr) {
     const float qx = x[3], qy = x[4], qz = x[5], qw = x[6];
-    tr.s1 = 2.f * (qw * qx + qy * qz);
-    tr.c1 = 1.f - 2.f * (qx * qx + qy * qy);
-    tr.s2 = 2.f * (qw * qy - qz * qx);
+    tr.s1 = 2.f * __builtin_fmaf(qy, qz, qw * qx);
+    tr.c1 = 2.f * __builtin_fmaf(-qy, qy, __builtin_fmaf(-qx, qx, 0.5f));
+    tr.s2 = 2.f * __builtin_fmaf(-qz, qx, qw * qy);
     const float roll = atan2_poly(tr.s1, tr.c1);
     const float pitch = asin_poly(fminf(fmaxf(tr.s2, -1.f), 1.f));
     const float ea0 = u[0] - roll, ea1 = u[1] - pitch;
-    cs[0] = x[17] + ea0 * dt;
-    cs[1] = x[18] + ea1 * dt;
+    cs[0] = __builtin_fmaf(ea0, dt, x[17]);
+    cs[1] = __builtin_fmaf(ea1, dt, x[18]);
     float rs[3];
-    rs[0] = C.akp[0] * ea0 + C.aki[0] * cs[0];
-    rs[1] = C.akp[1] * ea1 + C.aki[1] * cs[1];
+    rs[0] = __builtin_fmaf(C.akp[0], ea0, C.aki[0] * cs[0]);
+    rs[1] = __builtin_fmaf(C.akp[1], ea1, C.aki[1] * cs[1]);
     rs[2] = u[2];
     float tq[3];
 #pragma unroll
     for (int i = 0; i < 3; ++i) {
         const float w = x[10 + i];
         const float er = rs[i] - w;
-        cs[2 + i] = x[19 + i] + er * dt;
-        const float al = C.rkp[i] * er + C.rki[i] * cs[2 + i] - C.rkd[i] * (w - x[22 + i]) * inv_dt;
+        cs[2 + i] = __builtin_fmaf(er, dt, x[19 + i]);
+        const float al = __builtin_fmaf(-(C.rkd[i] * (w - x[22 + i])), inv_dt,
+                                        __builtin_fmaf(C.rkp[i], er, C.rki[i] * cs[2 + i]));
         tq[i] = C.jc[i] * al;
         cs[5 + i] = w;
     }
@@ -1660,8 +1671,8 @@ __device__ __forceinline__ void fp_step(float* x, float* comp, const float* u, c
     else
         integrate<S_FP, INTEG, COMP_FP>(x, comp, dt, [&](const float* xi, float* xd) { fp_rates(xi, rc, P, xd); });
     if (renorm) {
-        const float n2 = x[3] * x[3] + x[4] * x[4] + x[5] * x[5] + x[6] * x[6];
-        const float inv = rsqrt_hw(n2);
+        const float s0 = x[3] * x[3], s1 = x[4] * x[4], s2 = x[5] * x[5], s3 = x[6] * x[6];
+        const float inv = rsqrt_hw((s0 + s1) + (s2 + s3));
         x[3] *= inv; x[4] *= inv; x[5] *= inv; x[6] *= inv;
     }
 }
@@ -1697,11 +1708,12 @@ __device__ __forceinline__ void id_step_base(float* x, float* comp, const float*
     if (P.direct) x[12] = u[3];  // the thrust row holds the applied thrust
 }
 
-template <int INTEG>
-__device__ __forceinline__ void id_step(float* x, float* comp, const float* u, const IdParams& P, float dt) {
-    EulerBase B;
-    euler_base(x + 3, B);
-    id_step_base<INTEG>(x, comp, u, P, dt, B);
+// The start angles' sines and cosines B before step n of a run (a launch of held
+// steps, a rollout, a recomputed segment): exact every 8th step, in between carried
+// from the previous step by the angle addition.
+__device__ __forceinline__ void id_begin_step(const float* x, EulerBase& B, int n) {
+    if ((n & 7) == 0) euler_base(x + 3, B);
+    else euler_rebase(x + 3, B);
 }
 
 // adjoint of the renormalisation q_out = q / |q| that follows a step, given the

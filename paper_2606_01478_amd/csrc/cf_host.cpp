@@ -164,9 +164,9 @@ void derive_step(int model, float dt, float* out) {
         put(F_A2R, s * out[D_F4R]);
         const int mix[3] = {P_MIX_TX, P_MIX_TY, D_TZK}, to[3] = {F_TX, F_TY, F_TZ}, base[3] = {D_TXR, D_TYR, D_TZR};
         for (int a = 0; a < 3; ++a) {
-            const double J = out[P_J + a];
-            for (int i = 0; i < 4; ++i) put(to[a] + i, out[mix[a] + i] / (s * J));
-            put(F_TR + a, out[base[a]] / J);
+            const double iJ = 1.0 / out[P_J + a], scale = 0.5 * m * iJ;
+            for (int i = 0; i < 4; ++i) put(to[a] + i, out[mix[a] + i] * scale);
+            put(F_TR + a, out[base[a]] * iJ);
         }
         const double Jx = out[P_J], Jy = out[P_J + 1], Jz = out[P_J + 2];
         put(F_DJ, (Jz - Jy) / Jx);

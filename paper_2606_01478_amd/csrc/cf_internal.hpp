@@ -16,7 +16,20 @@ enum : int { MS_FP = 1, MS_ID = 2, MS_BOTH = 3 };
 //            model that may span worlds (a wave within one world reads its
 //            parameters with uniform loads, a wave across worlds per lane);
 //   LM_WQ:   persistent workgroups pop packed tiles from an atomic queue head.
-enum : int { LM_LANE = 0, LM_TILE = 1, LM_WQ = 2 };
+//   LM_QUAD: four lanes per drone (cf_quad.hip).
+enum : int { LM_LANE = 0, LM_TILE = 1, LM_WQ = 2, LM_QUAD = 3 };
+
+// Four lanes per drone up to so many drones per compute unit. 64 fill the SIMDs with
+// one wave each; beyond that waves share one and the extra lanes' work shows. Measured
+// (100 held steps, one lane -> four; 256 compute units):
+//   attitude controller  4096: 123 -> 55 us, 16384: 125 -> 60, 32768: 133 -> 101, 49152: 145 -> 144
+//   rotor interface      4096:  67 -> 40 us, 16384:  69 -> 43, 32768:  72 ->  72, 49152:  75 -> 102
+//   identified           4096:  65 -> 45 us, 16384:  66 -> 55, 32768:  69 ->  68, 49152:  70 ->  92
+// and of rollouts with their adjoint (50 steps, feedback): attitude controller 16384:
+// 457 -> 302 us, 32768: 489 -> 351, 49152: 535 -> 527; identified 16384: 304 -> 243,
+// 32768: 331 -> 296, 65536: 389 -> 455. A single step gains nothing beyond 16 per unit
+// (it is bound by its loads).
+constexpr int QUAD_HELD = 64, QUAD_HELD_PID = 128, QUAD_HELD_ONE = 16, QUAD_ROLL = 128;
 
 struct KernelSel {
     int models;  // MS_*
@@ -127,6 +140,13 @@ struct MppiArgs {
     float* u_apply;          // [4] or null
     int32_t* best;           // [1] or null
 };
+// One drone on four lanes (cf_quad.hip): handles of one model, reduced variants
+// (ks.aero == 0) under RK4, the rotor or attitude interface, the controller on every
+// step; rollouts with the tracking objective on the figure-eight and linear feedback.
+// S * D * 4 bytes must stay below 2^32.
+hipError_t launch_step_quad(const KernelSel& ks, const StepArgs& a, hipStream_t s);
+hipError_t launch_rollout_quad(const KernelSel& ks, const RollArgs& a, bool bwd, hipStream_t s);
+
 hipError_t launch_mppi_rollout(const KernelSel& ks, const MppiArgs& a, hipStream_t s);
 hipError_t launch_mppi_noise(const MppiArgs& a, hipStream_t s);
 hipError_t launch_mppi_select(const MppiArgs& a, hipStream_t s);

@@ -90,47 +90,69 @@ __global__ __launch_bounds__(256) void k_reduce_world(const float* __restrict__ 
     }
 }
 
-// Gain gradient g[k][c] = sum over drones d whose world uses gain k of
-// v[c][d] (c < 52), in a fixed order that depends only on D and the grid:
-// stage 1, workgroup b of gain k sums the drones of chunk b (each thread a
-// strided subset, then an LDS tree per component) into part[k][b][c];
-// stage 2 sums part[k][0..nb) in order. O(D / (nb 256) + log 256 + nb) deep.
+// g[k][c] = sum over the drones d whose world uses gain (or policy) k of v[c][d],
+// c < nc, in a fixed order that depends only on D: workgroup (b, c, k) sums the drones
+// of chunk b (each thread a strided subset, then a tree), into g directly where there
+// is one chunk, else into part[k][c][b], which k_sum_parts adds up. One workgroup per
+// component rather than one for all of them: the 52 trees one after the other, and the
+// serial sum over hundreds of chunks, took 108 us for 63 000 drones.
 constexpr int GAIN_COMP = 52;
 constexpr int GAIN_MAX_BLOCKS = 1024;
+constexpr int64_t SUM_CHUNK = 16384;
 
-__global__ __launch_bounds__(256) void k_gain_partial(const float* __restrict__ v, int64_t D,
-                                                      const int32_t* __restrict__ drone_world,
-                                                      const int32_t* __restrict__ gidx, int64_t chunk,
-                                                      float* __restrict__ part) {
-    __shared__ float sh[256];
-    const int b = blockIdx.x, k = blockIdx.y, nb = gridDim.x;
-    const int64_t lo = (int64_t)b * chunk, hi = min(D, lo + chunk);
-    float acc[GAIN_COMP];
+__global__ __launch_bounds__(1024) void k_sum_drones(const float* __restrict__ v, int64_t D,
+                                                     const int32_t* __restrict__ drone_world,
+                                                     const int32_t* __restrict__ gidx, int n_gains,
+                                                     float* __restrict__ out) {
+    __shared__ float sh[16];
+    const int b = blockIdx.x, nb = gridDim.x, c = blockIdx.y, nc = gridDim.y, k = blockIdx.z;
+    const int64_t lo = b * SUM_CHUNK, hi = min(D, lo + SUM_CHUNK);
+    const float* row = v + (size_t)c * D;
+    // four drones a thread at a time, so that their loads overlap
+    float s = 0.f;
+    for (int64_t d0 = lo + threadIdx.x; d0 < hi; d0 += 4096) {
+        float x[4];
+        bool mine[4];
 #pragma unroll
-    for (int c = 0; c < GAIN_COMP; ++c) acc[c] = 0.f;
-    for (int64_t d = lo + threadIdx.x; d < hi; d += blockDim.x) {
-        if (gidx[drone_world[d]] != k) continue;
-#pragma unroll
-        for (int c = 0; c < GAIN_COMP; ++c) acc[c] += v[(size_t)c * D + d];
-    }
-    for (int c = 0; c < GAIN_COMP; ++c) {
-        sh[threadIdx.x] = acc[c];
-        __syncthreads();
-        for (int h = blockDim.x / 2; h > 0; h >>= 1) {
-            if ((int)threadIdx.x < h) sh[threadIdx.x] += sh[threadIdx.x + h];
-            __syncthreads();
+        for (int i = 0; i < 4; ++i) {
+            const int64_t d = d0 + i * 1024;
+            mine[i] = d < hi && (n_gains == 1 || gidx[drone_world[d]] == k);
+            x[i] = d < hi ? row[d] : 0.f;
         }
-        if (threadIdx.x == 0) part[((size_t)k * nb + b) * GAIN_COMP + c] = sh[0];
-        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < 4; ++i) s += mine[i] ? x[i] : 0.f;
+    }
+#pragma unroll
+    for (int h = 32; h > 0; h >>= 1) s += __shfl_down(s, h, 64);
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = s;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        float t = 0.f;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) t += sh[i];
+        out[((size_t)k * nc + c) * nb + b] = t;
     }
 }
 
-__global__ void k_gain_final(const float* __restrict__ part, int nb, float* __restrict__ g) {
-    const int k = blockIdx.x, c = threadIdx.x;
-    if (c >= GAIN_COMP) return;
+__global__ __launch_bounds__(64) void k_sum_parts(const float* __restrict__ part, int nb, float* __restrict__ g) {
+    const float* p = part + (size_t)blockIdx.x * nb;
     float s = 0.f;
-    for (int b = 0; b < nb; ++b) s += part[((size_t)k * nb + b) * GAIN_COMP + c];
-    g[(size_t)k * GAIN_COMP + c] = s;
+    for (int b = threadIdx.x; b < nb; b += 64) s += p[b];
+#pragma unroll
+    for (int h = 32; h > 0; h >>= 1) s += __shfl_down(s, h, 64);
+    if (threadIdx.x == 0) g[blockIdx.x] = s;
+}
+
+// part: n_gains * nc * ceil(D / SUM_CHUNK) floats (unused with one chunk)
+static hipError_t sum_drones(const float* v, int nc, int64_t D, const int32_t* drone_world, const int32_t* gidx,
+                             int n_gains, float* part, float* g, hipStream_t s) {
+    const unsigned nb = (unsigned)((D + SUM_CHUNK - 1) / SUM_CHUNK);
+    hipLaunchKernelGGL(k_sum_drones, dim3(nb, nc, n_gains), dim3(1024), 0, s, v, D, drone_world, gidx, n_gains,
+                       nb == 1 ? g : part);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess || nb == 1) return e;
+    hipLaunchKernelGGL(k_sum_parts, dim3((unsigned)(n_gains * nc)), dim3(64), 0, s, part, (int)nb, g);
+    return hipGetLastError();
 }
 
 // Weight gradient of the small-MLP policies from the reverse sweep's records
@@ -1029,9 +1051,18 @@ static int roll_mode(const cf_handle* h) {
     return (h->lane_ok && h->D > 0 && (double)h->D / h->M < 32.0) ? LM_LANE : LM_TILE;
 }
 
-// rollouts on quads: the tracking objective on the figure-eight, linear feedback
-static bool quad_roll(const cf_handle* h, const RollArgs& a) {
-    return quad_ok(h, QUAD_ROLL) && a.obj_kind == 0 && !a.ref_user && !a.ref_shift && !a.squash && a.mlp_H == 0;
+// rollouts on quads: the figure-eight with the tracking objective and linear feedback;
+// the identified model also the reward, time shifts, squashed outputs and the MLP policy
+// (where its padded copy fits in LDS)
+static bool quad_roll(const cf_handle* h, const cf_objective* obj) {
+    if (!quad_ok(h, QUAD_ROLL)) return false;
+    if (!obj) return true;
+    if (obj->ref_table) return false;
+    bool squash = false;
+    for (float s : obj->policy_scale) squash = squash || s > 0.f;
+    const bool ext = obj->kind == CF_OBJ_BPTT_REWARD || obj->ref_time_shift || squash || obj->policy_hidden > 0;
+    if (!ext) return true;
+    return h->models == MS_ID && (obj->policy_hidden <= 0 || quad_policy_lds(obj->policy_hidden, h->n_gains) <= 65536);
 }
 
 // ref_tab_buf: device [(T + 1)][6] for the figure-eight table, or null to use the
@@ -1200,7 +1231,7 @@ cf_status cf_rollout(cf_handle* h, const float* x0, const float* cmds, int32_t T
         a.loss = (float*)h->loss_tmp.p;
     }
     if (h->D > 0) {
-        const bool quad = quad_roll(h, a);
+        const bool quad = quad_roll(h, obj);
         const int mode = roll_mode(h);
         if (!quad && mode == LM_TILE && (e = build_tiles(h, h->tile)) != hipSuccess) return note(h, e);
         e = per_model(h, h->stream, h->split, [&](int models, const int4* tiles, int nt, hipStream_t st, int) {
@@ -1274,7 +1305,10 @@ static cf_status rollout_backward_impl(cf_handle* h, const float* cmds, int32_t 
     const int64_t N_rec = (int64_t)T * Dm;
     const int nb_mlp = (int)std::max<int64_t>(1, std::min<int64_t>((N_rec + 2047) / 2048, GAIN_MAX_BLOCKS));
     const size_t n_ggc = (g_gain && Hp == 0) ? (size_t)52 * Dm : 0;
-    const size_t n_rec = (g_gain && Hp > 0) ? (size_t)(17 + 4 * Hp) * N_rec : 0;
+    // policies: records of every drone-step, or (quad kernels) each drone's own sum of
+    // its weight gradient where that is less
+    const bool pol_sum = Hp > 0 && quad_sums_policy(Hp) && (int64_t)Pp <= (int64_t)(17 + 4 * Hp) * T && quad_roll(h, obj);
+    const size_t n_rec = (g_gain && Hp > 0) ? (pol_sum ? (size_t)Pp * Dm : (size_t)(17 + 4 * Hp) * N_rec) : 0;
     const size_t n_part = !g_gain ? 0
                                   : (Hp > 0 ? (size_t)h->n_gains * nb_mlp * Pp : (size_t)h->n_gains * nb * GAIN_COMP);
     hipSetDevice(h->device);
@@ -1325,7 +1359,8 @@ static cf_status rollout_backward_impl(cf_handle* h, const float* cmds, int32_t 
     a.ggc = (g_gain && Hp == 0) ? sc.ggc : nullptr;
     a.mlp_rec = (g_gain && Hp > 0) ? sc.rec : nullptr;
     if (h->D > 0) {
-        const bool quad = quad_roll(h, a);
+        // a policy whose records are wanted but would be summed goes the general way
+        const bool quad = quad_roll(h, obj) && !(Hp > 0 && quad_sums_policy(Hp) && !pol_sum);
         const int mode = roll_mode(h);
         if (!quad && mode == LM_TILE && (e = build_tiles(h, h->tile)) != hipSuccess) return note(h, e);
         e = per_model(h, h->stream, h->split, [&](int models, const int4* tiles, int nt, hipStream_t st, int) {
@@ -1336,7 +1371,10 @@ static cf_status rollout_backward_impl(cf_handle* h, const float* cmds, int32_t 
         });
         if (e != hipSuccess) return note(h, e);
     }
-    if (g_gain && Hp > 0) {
+    if (g_gain && pol_sum && h->D > 0) {
+        e = sum_drones(sc.rec, Pp, h->D, h->drone_world, h->d_gidx, h->n_gains, sc.gpart, g_gain, h->stream);
+        if (e != hipSuccess) return note(h, e);
+    } else if (g_gain && Hp > 0) {
         if (h->D > 0) {
             const int64_t chunk = (N_rec + nb_mlp - 1) / nb_mlp;
             hipLaunchKernelGGL(k_mlp_partial, dim3(nb_mlp, h->n_gains), dim3(256),
@@ -1352,12 +1390,8 @@ static cf_status rollout_backward_impl(cf_handle* h, const float* cmds, int32_t 
         if ((e = hipGetLastError()) != hipSuccess) return note(h, e);
     } else if (g_gain) {
         if (h->D > 0) {
-            const int64_t chunk = (h->D + nb - 1) / nb;
-            hipLaunchKernelGGL(k_gain_partial, dim3(nb, h->n_gains), dim3(256), 0, h->stream, (const float*)sc.ggc,
-                               h->D, h->drone_world, h->d_gidx, chunk, sc.gpart);
-            if ((e = hipGetLastError()) != hipSuccess) return note(h, e);
-            hipLaunchKernelGGL(k_gain_final, dim3(h->n_gains), dim3(64), 0, h->stream, (const float*)sc.gpart, nb,
-                               g_gain);
+            e = sum_drones(sc.ggc, GAIN_COMP, h->D, h->drone_world, h->d_gidx, h->n_gains, sc.gpart, g_gain, h->stream);
+            if (e != hipSuccess) return note(h, e);
         } else {
             hipLaunchKernelGGL(k_fill_u32, dim3((h->n_gains * 52 + 255) / 256), dim3(256), 0, h->stream,
                                (unsigned*)g_gain, h->n_gains * 52, 0u);

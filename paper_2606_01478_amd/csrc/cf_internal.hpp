@@ -142,10 +142,15 @@ struct MppiArgs {
 };
 // One drone on four lanes (cf_quad.hip): handles of one model, reduced variants
 // (ks.aero == 0) under RK4, the rotor or attitude interface, the controller on every
-// step; rollouts with the tracking objective on the figure-eight and linear feedback.
-// S * D * 4 bytes must stay below 2^32.
+// step; rollouts on the figure-eight with the tracking objective and linear feedback,
+// of the identified model also with the reward objective, time shifts, squashed outputs
+// and the small-MLP policy. S * D * 4 bytes must stay below 2^32.
 hipError_t launch_step_quad(const KernelSel& ks, const StepArgs& a, hipStream_t s);
 hipError_t launch_rollout_quad(const KernelSel& ks, const RollArgs& a, bool bwd, hipStream_t s);
+// LDS of n_pol policies of width H, and whether the backward sums each drone's weight
+// gradient itself (RollArgs::mlp_rec is then [P][D]) instead of writing records
+size_t quad_policy_lds(int H, int n_pol);
+bool quad_sums_policy(int H);
 
 hipError_t launch_mppi_rollout(const KernelSel& ks, const MppiArgs& a, hipStream_t s);
 hipError_t launch_mppi_noise(const MppiArgs& a, hipStream_t s);

@@ -11,6 +11,7 @@ import oracle as O
 import workloads as W
 from gpu_helpers import assert_states_close, dev
 from paper_2606_01478_amd import binding as B
+from test_gpu_mlp import _grads
 from test_gpu_parity import _check_against_oracle, _rollout_grads, _sim
 
 pytestmark = pytest.mark.gpu
@@ -68,3 +69,14 @@ def test_nonfinite_world_is_flagged(gpu_lib):
     sim.step_k(x, dev(w.cmds[0]), 3, nonfinite=flag)
     torch.cuda.synchronize()
     assert flag[20] == 1 and int(flag.sum()) == 1
+
+
+@pytest.mark.parametrize("hidden,T", [(5, 30), (13, 30), (16, 3), (31, 12)])
+def test_two_policies_of_odd_width(gpu_lib, hidden, T):
+    """Padded units, two policies in one batch, and (T = 3) a horizon so short that
+    records take less scratch than each drone's own sum of the weight gradient."""
+    w = W.id_rollout_grad_mlp(seed=90 + hidden, n_worlds=21, steps=T, hidden=hidden, out_scale=0.05)
+    rng = np.random.Generator(np.random.Philox(hidden))
+    w = dataclasses.replace(w, gain=W.mlp_policy_params(rng, 2, hidden, 0.05),
+                            gain_index=(np.arange(21) % 2).astype(np.int32))
+    _check_against_oracle(w, _grads(_sim(w), w, 7))

@@ -1301,25 +1301,34 @@ static cf_status rollout_backward_impl(cf_handle* h, const float* cmds, int32_t 
     const int slots = std::min(K, T) + (kind == CF_OBJ_BPTT_REWARD ? 1 : 0);
     const int nb = gain_blocks(h->D);
     const size_t n_tab = (obj && !obj->ref_table) ? (size_t)(T + 1) * 6 : 0;
-    const size_t n_seg = slots > 1 ? (size_t)slots * h->S * Dm : 0;
+    const bool quad_b = quad_roll(h, obj);
+    // quads recompute every segment at once where the states fit (QUAD_SEG_FLOATS) and
+    // there are enough of them to pay for the launch
+    const size_t n_all = (size_t)(T + 1) * h->S * Dm;
+    bool seg_all = quad_b && K > 1 && T > K && T >= 16 && n_all <= QUAD_SEG_FLOATS && (T + K - 1) / K <= 65535;
     const int64_t N_rec = (int64_t)T * Dm;
     const int nb_mlp = (int)std::max<int64_t>(1, std::min<int64_t>((N_rec + 2047) / 2048, GAIN_MAX_BLOCKS));
     const size_t n_ggc = (g_gain && Hp == 0) ? (size_t)52 * Dm : 0;
     // policies: records of every drone-step, or (quad kernels) each drone's own sum of
     // its weight gradient where that is less
-    const bool pol_sum = Hp > 0 && quad_sums_policy(Hp) && (int64_t)Pp <= (int64_t)(17 + 4 * Hp) * T && quad_roll(h, obj);
+    const bool pol_sum = Hp > 0 && quad_sums_policy(Hp) && (int64_t)Pp <= (int64_t)(17 + 4 * Hp) * T && quad_b;
     const size_t n_rec = (g_gain && Hp > 0) ? (pol_sum ? (size_t)Pp * Dm : (size_t)(17 + 4 * Hp) * N_rec) : 0;
     const size_t n_part = !g_gain ? 0
                                   : (Hp > 0 ? (size_t)h->n_gains * nb_mlp * Pp : (size_t)h->n_gains * nb * GAIN_COMP);
+    // a policy whose records are wanted but would be summed goes the general way
+    const bool quad = quad_b && !(Hp > 0 && quad_sums_policy(Hp) && !pol_sum);
+    auto up = [](size_t n) { return (n + 63) / 64 * 64; };   // 256-byte-aligned slices
+    const size_t cap = CF_NOALLOC_SCRATCH_BYTES / sizeof(float);
+    seg_all = seg_all && quad &&
+              (!noalloc || up(n_tab) + up(n_all) + up(n_ggc) + up(n_rec) + up(n_part) <= cap);
+    const size_t n_seg = seg_all ? n_all : (slots > 1 ? (size_t)slots * h->S * Dm : 0);
     hipSetDevice(h->device);
     hipError_t e;
     BwdScratch sc;
     if (noalloc) {
         float* base = scratch_of(h->device);
         if (!base) return CF_EUNSUPPORTED;
-        // 256-byte-aligned slices; sizes beyond the array are refused before any work
-        auto up = [](size_t n) { return (n + 63) / 64 * 64; };
-        const size_t cap = CF_NOALLOC_SCRATCH_BYTES / sizeof(float);
+        // sizes beyond the array are refused before any work
         if (up(n_tab) + up(n_seg) + up(n_ggc) + up(n_rec) + up(n_part) > cap) return CF_EINVAL;
         float* q = base;
         auto take = [&](size_t n) -> float* {
@@ -1356,11 +1365,10 @@ static cf_status rollout_backward_impl(cf_handle* h, const float* cmds, int32_t 
     a.g_cmds = g_cmds;
     a.g_x0 = g_x0;
     a.seg = n_seg ? sc.seg : nullptr;
+    a.seg_all = seg_all ? 1 : 0;
     a.ggc = (g_gain && Hp == 0) ? sc.ggc : nullptr;
     a.mlp_rec = (g_gain && Hp > 0) ? sc.rec : nullptr;
     if (h->D > 0) {
-        // a policy whose records are wanted but would be summed goes the general way
-        const bool quad = quad_roll(h, obj) && !(Hp > 0 && quad_sums_policy(Hp) && !pol_sum);
         const int mode = roll_mode(h);
         if (!quad && mode == LM_TILE && (e = build_tiles(h, h->tile)) != hipSuccess) return note(h, e);
         e = per_model(h, h->stream, h->split, [&](int models, const int4* tiles, int nt, hipStream_t st, int) {

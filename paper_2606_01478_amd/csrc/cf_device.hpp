@@ -378,17 +378,13 @@ __device__ __forceinline__ void sincos_slow(const float* a, float* s, float* c) 
 }
 
 // sines and cosines of the three Euler angles; arguments beyond 2^15 rad (never
-// reached by the workloads) take the library routine
+// reached by the workloads) take the library routine, which overwrites the short
+// evaluation: the common path is straight-line code with one branch past the rare one
 __device__ __forceinline__ void sincos3(const float* a, float* s, float* c) {
     const float m = fmaxf(fabsf(a[0]), fmaxf(fabsf(a[1]), fabsf(a[2])));
-    if (__builtin_expect(m > 32768.f, 0)) {
 #pragma unroll
-        for (int i = 0; i < 3; ++i) { s[i] = 0.f; c[i] = 0.f; }
-        sincos_slow<3>(a, s, c);
-    } else {
-#pragma unroll
-        for (int i = 0; i < 3; ++i) sincos_cw(a[i], s + i, c + i);
-    }
+    for (int i = 0; i < 3; ++i) sincos_cw(a[i], s + i, c + i);
+    if (__builtin_expect(m > 32768.f, 0)) sincos_slow<3>(a, s, c);
 }
 
 // Euler-angle trigonometry of RK4 stage states. A stage's angles differ from
@@ -412,21 +408,19 @@ template <int N>
 __device__ __forceinline__ void sincos_off(const float* d, const EulerBase& b, float* s, float* c) {
     float m = 0.f;
 #pragma unroll
-    for (int i = 0; i < N; ++i) m = fmaxf(m, fabsf(d[i]));
-    if (__builtin_expect(m <= 0.0625f, 1)) {
-#pragma unroll
-        for (int i = 0; i < N; ++i) {
-            const float s0 = b.s0[i % 3], c0 = b.c0[i % 3];
-            const float d2 = d[i] * d[i];
-            const float sd = __builtin_fmaf(d[i] * d2, __builtin_fmaf(d2, 1.f / 120.f, -1.f / 6.f), d[i]);
-            const float cm1 = d2 * __builtin_fmaf(d2, __builtin_fmaf(d2, -1.f / 720.f, 1.f / 24.f), -0.5f);
-            s[i] = __builtin_fmaf(s0, cm1, __builtin_fmaf(c0, sd, s0));
-            c[i] = __builtin_fmaf(c0, cm1, __builtin_fmaf(-s0, sd, c0));
-        }
-    } else {
+    for (int i = 0; i < N; ++i) {
+        m = fmaxf(m, fabsf(d[i]));
+        const float s0 = b.s0[i % 3], c0 = b.c0[i % 3];
+        const float d2 = d[i] * d[i];
+        const float sd = __builtin_fmaf(d[i] * d2, __builtin_fmaf(d2, 1.f / 120.f, -1.f / 6.f), d[i]);
+        const float cm1 = d2 * __builtin_fmaf(d2, __builtin_fmaf(d2, -1.f / 720.f, 1.f / 24.f), -0.5f);
+        s[i] = __builtin_fmaf(s0, cm1, __builtin_fmaf(c0, sd, s0));
+        c[i] = __builtin_fmaf(c0, cm1, __builtin_fmaf(-s0, sd, c0));
+    }
+    if (__builtin_expect(m > 0.0625f, 0)) {
         float a[N];
 #pragma unroll
-        for (int i = 0; i < N; ++i) { a[i] = b.a0[i % 3] + d[i]; s[i] = 0.f; c[i] = 0.f; }
+        for (int i = 0; i < N; ++i) a[i] = b.a0[i % 3] + d[i];
         sincos_slow<N>(a, s, c);
     }
 }

@@ -29,6 +29,7 @@ enum : int { LM_LANE = 0, LM_TILE = 1, LM_WQ = 2, LM_QUAD = 3 };
 // 457 -> 302 us, 32768: 489 -> 351, 49152: 535 -> 527; identified 16384: 304 -> 243,
 // 32768: 331 -> 296, 65536: 389 -> 455. A single step gains nothing beyond 16 per unit
 // (it is bound by its loads).
+constexpr size_t QUAD_SEG_FLOATS = (size_t)64 << 20;   // states kept at once by the adjoint: 256 MiB
 constexpr int QUAD_HELD = 64, QUAD_HELD_PID = 128, QUAD_HELD_ONE = 16, QUAD_ROLL = 128;
 
 struct KernelSel {
@@ -108,7 +109,9 @@ struct RollArgs {
     float* g_cmds;          // [T][4][D] or null
     float* g_x0;            // [S][D] or null
     float* ggc;             // [52][D] per-drone gain-gradient contributions or null
-    float* seg;             // [K][S][D] segment scratch
+    float* seg;             // [K][S][D] segment scratch, or (seg_all, quad kernels) [T + 1][S][D]:
+                            // every state between the checkpoints, and the final one
+    int seg_all;
 };
 
 // sampled-rollout controller (one world's model, C controllers x N samples)

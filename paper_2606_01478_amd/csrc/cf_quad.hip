@@ -283,21 +283,20 @@ __global__ __launch_bounds__(64) void k_quad_step(StepArgs a) {
 // time shift in the extended kernels (x runs at w, y at 2 w: see RefLane) and its offset
 template <bool EXT>
 struct QRef {
-    const float* tab;
+    const float* tab;   // lane 3 reads lane 2's column (zeros)
     float off, c, s, w, iw;
-    int j;
     bool on;
     __device__ __forceinline__ QRef(const RollArgs& a, const QLane& L)
-        : tab(a.ref_tab), off(0.f), c(1.f), s(0.f), w(0.f), iw(0.f), j(L.j), on(a.has_obj && L.j < 3) {
-        if (on && a.ref_off) off = q_load(a.ref_off, L.row(0));
+        : tab(a.ref_tab + (L.j < 3 ? L.j : 2)), off(0.f), c(1.f), s(0.f), w(0.f), iw(0.f), on(a.has_obj) {
+        if (on && a.ref_off && L.j < 3) off = q_load(a.ref_off, L.row(0));
         if constexpr (EXT) {
-            if (on && a.ref_shift && j < 2) {
+            if (on && a.ref_shift && L.j < 2) {
                 float s1, c1;
                 sincosf(a.ref_w * a.ref_shift[L.d], &s1, &c1);
-                c = j == 0 ? c1 : c1 * c1 - s1 * s1;
-                s = j == 0 ? s1 : 2.f * s1 * c1;
-                w = j == 0 ? a.ref_w : 2.f * a.ref_w;
-                iw = j == 0 ? a.ref_inv_w : 0.5f * a.ref_inv_w;
+                c = L.j == 0 ? c1 : c1 * c1 - s1 * s1;
+                s = L.j == 0 ? s1 : 2.f * s1 * c1;
+                w = L.j == 0 ? a.ref_w : 2.f * a.ref_w;
+                iw = L.j == 0 ? a.ref_inv_w : 0.5f * a.ref_inv_w;
             }
         }
     }
@@ -305,7 +304,7 @@ struct QRef {
         *p = 0.f;
         *v = 0.f;
         if (on) {
-            const float* r = tab + (size_t)t * 6 + j;
+            const float* r = tab + (size_t)t * 6;
             if constexpr (EXT) {
                 const float p0 = r[0], v0 = r[3];
                 *p = fma_(p0, c, (v0 * iw) * s) + off;
@@ -546,6 +545,84 @@ __global__ __launch_bounds__(64) void k_quad_fwd(RollArgs a) {
     }
 }
 
+// The applied command of the adjoint's recompute and reverse sweeps; e: the policy's
+// input, h1, h2: its activations, o: its output.
+template <class Q, bool EXT, int U>
+__device__ __forceinline__ float q_command(const RollArgs& a, const Q& m, bool fb, const float* g, lds_float* pol,
+                                           const typename Q::State& s, int j, float ubar, float rp, float rv, float* e,
+                                           float* h1, float* h2, float* o) {
+    if (!fb && U == 0) return ubar;
+    m.error(s, rp, rv, j, e);
+    if constexpr (U > 0) *o = q_mlp_forward<Q, U>(q_again(pol), e, j, h1, h2);
+    else *o = Q::dot13(g, e);
+    if (EXT && a.squash) return fma_(a.act_s[j], tanhf(*o), ubar);
+    return ubar + *o;
+}
+
+// Recompute steps t0 .. t0 + n of a segment from its checkpoint, storing the states of
+// all but the last into the slots after `slot`; the last too where `last`.
+template <class Q, bool EXT, int U>
+__device__ __forceinline__ void q_recompute(const RollArgs& a, Q& m, const QLane& L, bool fb, const float* g,
+                                            lds_float* pol, const QRef<EXT>& ref, const float* ck, int t0, int n,
+                                            int n_store, float* slot, typename Q::State& x) {
+    const size_t D = (size_t)a.D, SD = (size_t)a.S_h * D;
+    constexpr int UM = U == 0 ? 2 : U;
+    const uint32_t uo = L.row(0);
+    m.template load<true>(ck, L, x);
+    m.begin(x);
+    const float* cmd = a.cmds + (size_t)t0 * 4 * D;
+    float ubar = q_load(cmd, uo), rp, rv;
+    ref.at(t0, &rp, &rv);
+    for (int i = 0; i < n; ++i) {
+        cmd += 4 * D;
+        float un = 0.f, rpn = 0.f, rvn = 0.f;
+        if (i + 1 < n) {   // the next step's, issued early
+            un = q_load(cmd, uo);
+            ref.at(t0 + i + 1, &rpn, &rvn);
+        }
+        float e[4], h1[UM], h2[UM], o;
+        const float u = q_command<Q, EXT, U>(a, m, fb, g, pol, x, L.j, ubar, rp, rv, e, h1, h2, &o);
+        m.step(x, u, a.dt, a.renorm, L.j, i);
+        slot += SD;
+        if (i < n_store) m.template store<false>(slot, L, x);
+        ubar = un;
+        rp = rpn;
+        rv = rvn;
+    }
+}
+
+// The states between the checkpoints, every segment at once: blockIdx.y is the
+// segment. One drone's segments are independent given their checkpoints, and a small
+// batch leaves the SIMDs to run them side by side: the adjoint's chain is then the
+// reverse sweep alone (1024 identified drones, 500 steps, checkpoint every 50: 836 ->
+// 560 us). Slot t of a.seg receives x_t; slot T the final state.
+template <int MODEL, int CTRL, bool EXT, int U>
+__global__ __launch_bounds__(64) void k_quad_segments(RollArgs a) {
+    extern __shared__ __align__(16) float q_lds[];
+    if constexpr (U > 0) {
+        for (int k = 0; k < a.n_pol; ++k)
+            QMlp<U>::template stage<false>(a.gain + (size_t)k * a.mlp_P, a.mlp_H, q_lds + k * QMlp<U>::FWD);
+        __syncthreads();
+    }
+    const uint32_t d = blockIdx.x * 16u + threadIdx.x / 4u;
+    if (d >= (uint32_t)a.D || !ckpt_tag_intact(a)) return;
+    const QLane L{(int)(threadIdx.x & 3u), d, (uint32_t)a.D};
+    const int w = a.drone_world[d];
+    const size_t SD = (size_t)a.S_h * a.D;
+    using Q = QDrone<MODEL, CTRL>;
+    Q m(LaneRec{a.par_aos + (size_t)w * NREC}, L.j, a.dt, a.inv_dtc);
+    const bool fb = U == 0 && a.has_obj && a.gain;
+    float g[13];
+    if (fb) q_gain_row(a.gain + (size_t)a.gidx[w] * NG, L.j, g);
+    lds_float* pol = U > 0 ? (lds_float*)q_lds + a.gidx[w] * QMlp<U == 0 ? 2 : U>::FWD : nullptr;
+    const QRef<EXT> ref(a, L);
+    const int t0 = blockIdx.y * a.K, t1 = min(a.T, t0 + a.K);
+    const int n = t1 == a.T ? t1 - t0 : t1 - t0 - 1;
+    typename Q::State x;
+    q_recompute<Q, EXT, U>(a, m, L, fb, g, pol, ref, a.ckpt_in + (size_t)blockIdx.y * SD, t0, n, n,
+                           a.seg + (size_t)t0 * SD, x);
+}
+
 template <int MODEL, int CTRL, bool EXT, int U>
 __global__ __launch_bounds__(64) void k_quad_bwd(RollArgs a) {
     rollout_priority();
@@ -614,16 +691,6 @@ __global__ __launch_bounds__(64) void k_quad_bwd(RollArgs a) {
     float ah = 0.f;
     if constexpr (EXT) ah = q_hover(m, j);
     const uint32_t uo = L.row(0);
-    // the applied command; e: the policy's input, h1, h2: its activations, o: its output
-    const auto command = [&](const typename Q::State& s, float ubar, float rp, float rv, float* e, float* h1, float* h2,
-                             float* o) {
-        if (!fb && U == 0) return ubar;
-        m.error(s, rp, rv, j, e);
-        if constexpr (U > 0) *o = q_mlp_forward<Q, UM>(q_again(pol), e, j, h1, h2);
-        else *o = Q::dot13(g, e);
-        if (EXT && a.squash) return fma_(a.act_s[j], tanhf(*o), ubar);
-        return ubar + *o;
-    };
     typename Q::Adj lam;
     Q::zero(lam);
     const int nseg = (a.T + a.K - 1) / a.K;
@@ -639,24 +706,20 @@ __global__ __launch_bounds__(64) void k_quad_bwd(RollArgs a) {
         const int t0 = sg * a.K;
         const int t1 = min(a.T, t0 + a.K);
         const float* ck = a.ckpt_in + (size_t)sg * SD;
+        float* const slots = a.seg_all ? a.seg + (size_t)t0 * SD : a.seg;
         // recompute x_{t0+1} .. x_{t1-1} into segment slots 1..; slot 0 is the
         // checkpoint. The last segment steps once more for the final position.
         const int n_re = (sg == nseg - 1) ? (t1 - t0) : (t1 - t0 - 1);
-        if (n_re > 0) {
-            typename Q::State x;
-            m.template load<true>(ck, L, x);
-            m.begin(x);
-            float* slot = a.seg;
-            const float* cmd = a.cmds + (size_t)t0 * 4 * D;
-            for (int i = 0; i < n_re; ++i) {
-                float e[4], h1[UM], h2[UM], o, p, v;
-                ref.at(t0 + i, &p, &v);
-                const float u = command(x, q_load(cmd, uo), p, v, e, h1, h2, &o);
-                m.step(x, u, a.dt, a.renorm, j, i);
-                cmd += 4 * D;
-                slot += SD;
-                if (i + 1 < t1 - t0) m.template store<false>(slot, L, x);
+        if (a.seg_all) {
+            if (sg == nseg - 1) {   // done by k_quad_segments
+                typename Q::State x;
+                m.template load<false>(slots + (size_t)(t1 - t0) * SD, L, x);
+                pn = Q::pos(x);
+                if constexpr (EXT) an = x.x.a;
             }
+        } else if (n_re > 0) {
+            typename Q::State x;
+            q_recompute<Q, EXT, U>(a, m, L, fb, g, pol, ref, ck, t0, n_re, t1 - t0 - 1, slots, x);
             if (sg == nseg - 1) {
                 pn = Q::pos(x);
                 if constexpr (EXT) an = x.x.a;
@@ -668,15 +731,17 @@ __global__ __launch_bounds__(64) void k_quad_bwd(RollArgs a) {
             xc = xq;
             uc = uq;
         } else {
-            if (t1 - 1 > t0) m.template load<false>(a.seg + (size_t)(t1 - 1 - t0) * SD, L, xc);
+            if (t1 - 1 > t0) m.template load<false>(slots + (size_t)(t1 - 1 - t0) * SD, L, xc);
             else m.template load<true>(ck, L, xc);
             uc = q_load(a.cmds + (size_t)(t1 - 1) * 4 * D, uo);
         }
         for (int t = t1 - 1; t >= t0; --t) {
             have_q = false;
-            const bool more = t > t0 || (a.K == 1 && sg > 0);
+            // (across a segment's start too, where the states before it are there)
+            const bool more = t > t0 || ((a.K == 1 || a.seg_all) && sg > 0);
             if (more) {
-                if (t - 1 > t0) m.template load<false>(a.seg + (size_t)(t - 1 - t0) * SD, L, xq);
+                const bool in_slot = t > t0 ? t - 1 > t0 : a.K > 1;
+                if (in_slot) m.template load<false>(slots + (ptrdiff_t)(t - 1 - t0) * (ptrdiff_t)SD, L, xq);
                 else m.template load<true>(t > t0 ? ck : ck - SD, L, xq);
                 uq = q_load(a.cmds + (size_t)(t - 1) * 4 * D, uo);
                 have_q = true;
@@ -701,7 +766,7 @@ __global__ __launch_bounds__(64) void k_quad_bwd(RollArgs a) {
                 }
             }
             float e[4], h1[UM], h2[UM], o = 0.f, ub = 0.f;
-            const float u = command(xc, uc, rp, rv, e, h1, h2, &o);
+            const float u = q_command<Q, EXT, U>(a, m, fb, g, pol, xc, j, uc, rp, rv, e, h1, h2, &o);
             m.vjp(back, xc, u, a.dt, a.renorm, j, lam, &ub);
             if (rew) {
                 // (u_t - u_hover)^2, (u_t - u_{t-1})^2 and, from the next step, (u_{t+1} - u_t)^2
@@ -820,7 +885,14 @@ template <int MODEL, int CTRL, bool EXT, int U>
 static hipError_t launch_roll_q(const RollArgs& a, bool bwd, hipStream_t s) {
     const dim3 grid((unsigned)((a.D + 15) / 16));
     const size_t lds = U == 0 ? 0 : sizeof(float) * a.n_pol * (bwd ? QMlp<U == 0 ? 2 : U>::BWD : QMlp<U == 0 ? 2 : U>::FWD);
-    if (bwd) hipLaunchKernelGGL((k_quad_bwd<MODEL, CTRL, EXT, U>), grid, dim3(64), lds, s, a);
+    if (bwd) {
+        if (a.seg_all) {
+            const size_t fwd_lds = U == 0 ? 0 : sizeof(float) * a.n_pol * QMlp<U == 0 ? 2 : U>::FWD;
+            const dim3 segments(grid.x, (unsigned)((a.T + a.K - 1) / a.K));
+            hipLaunchKernelGGL((k_quad_segments<MODEL, CTRL, EXT, U>), segments, dim3(64), fwd_lds, s, a);
+        }
+        hipLaunchKernelGGL((k_quad_bwd<MODEL, CTRL, EXT, U>), grid, dim3(64), lds, s, a);
+    }
     else hipLaunchKernelGGL((k_quad_fwd<MODEL, CTRL, EXT, U>), grid, dim3(64), lds, s, a);
     return hipGetLastError();
 }

@@ -407,40 +407,31 @@ __device__ __forceinline__ QIdBack q_load_id_back(const R& rec) {
 }
 
 __device__ __forceinline__ void q_sincos(float a, float* s, float* c) {
+    sincos_cw(a, s, c);
     if (__builtin_expect(fabsf(a) > 32768.f, 0)) sincosf(a, s, c);
-    else sincos_cw(a, s, c);
 }
 
-// sines and cosines at N offsets from the base angle; beyond 1/16 rad in full
+// sines and cosines at N offsets from the base angle; beyond 1/16 rad on any axis in
+// full (as one lane per drone decides)
 template <int N>
 __device__ __forceinline__ void q_sincos_off(const float* d, const QIdBase& b, float* s, float* c) {
     float m = 0.f;
 #pragma unroll
-    for (int i = 0; i < N; ++i) m = fmaxf(m, fabsf(d[i]));
-    m = fmaxf(m, qperm<1, 0, 3, 2>(m));   // of all axes, as one lane per drone decides
+    for (int i = 0; i < N; ++i) {
+        m = fmaxf(m, fabsf(d[i]));
+        const float d2 = d[i] * d[i];
+        const float sd = fma_(d[i] * d2, fma_(d2, 1.f / 120.f, -1.f / 6.f), d[i]);
+        const float cm1 = d2 * fma_(d2, fma_(d2, -1.f / 720.f, 1.f / 24.f), -0.5f);
+        s[i] = fma_(b.s0, cm1, fma_(b.c0, sd, b.s0));
+        c[i] = fma_(b.c0, cm1, fma_(-b.s0, sd, b.c0));
+    }
+    m = fmaxf(m, qperm<1, 0, 3, 2>(m));
     m = fmaxf(m, qperm<2, 3, 0, 1>(m));
-    if (__builtin_expect(m <= 0.0625f, 1)) {
-#pragma unroll
-        for (int i = 0; i < N; ++i) {
-            const float d2 = d[i] * d[i];
-            const float sd = fma_(d[i] * d2, fma_(d2, 1.f / 120.f, -1.f / 6.f), d[i]);
-            const float cm1 = d2 * fma_(d2, fma_(d2, -1.f / 720.f, 1.f / 24.f), -0.5f);
-            s[i] = fma_(b.s0, cm1, fma_(b.c0, sd, b.s0));
-            c[i] = fma_(b.c0, cm1, fma_(-b.s0, sd, b.c0));
-        }
-    } else {
+    if (__builtin_expect(m > 0.0625f, 0)) {
         float r[N];
 #pragma unroll
-        for (int i = 0; i < N; ++i) { r[i] = b.a0 + d[i]; s[i] = 0.f; c[i] = 0.f; }
-#pragma unroll 1
-        for (int n = 0; n < N; ++n) {   // rotating registers: one copy of the full evaluation
-            float sv, cv;
-            q_sincos(r[0], &sv, &cv);
-#pragma unroll
-            for (int i = 0; i + 1 < N; ++i) { r[i] = r[i + 1]; s[i] = s[i + 1]; c[i] = c[i + 1]; }
-            s[N - 1] = sv;
-            c[N - 1] = cv;
-        }
+        for (int i = 0; i < N; ++i) r[i] = b.a0 + d[i];
+        sincos_slow<N>(r, s, c);
     }
 }
 __device__ __forceinline__ void q_id_base(float a, QIdBase& b) {

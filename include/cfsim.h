@@ -504,7 +504,7 @@ typedef struct cf_mppi_desc {
  * cf_mppi_create: a controller set for the single world of handle h (h must
  * have n_worlds = 1; its parameters, model, interface, integrator and dt are
  * used; h must outlive the controller set and its stream is used). Allocates
- * device scratch of about C*N*4 + C*n_e*(16*H + 8) bytes.
+ * device scratch of about C*N*4 + C*n_e*8 + C*ceil(n_e/64)*(16*H + 4) bytes.
  * Errors: CF_EINVAL (h has more than one world, a field out of range or not
  * finite), CF_ENOMEM; *out is NULL on failure.
  */

@@ -33,6 +33,20 @@ __global__ void k_fill_u32(unsigned* p, int n, unsigned v) {
     if (i < n) p[i] = v;
 }
 
+// soa[i][w] = aos[w][i] of the parameter records
+__global__ __launch_bounds__(64) void k_transpose_records(const float* __restrict__ aos, int M, float* __restrict__ soa) {
+    const int w = blockIdx.x * 64 + threadIdx.x;
+    if (w >= M) return;
+    const float4* r = (const float4*)(aos + (size_t)w * NREC);
+    for (int i = 0; i < NREC / 4; ++i) {
+        const float4 v = r[i];
+        soa[(size_t)(4 * i) * M + w] = v.x;
+        soa[(size_t)(4 * i + 1) * M + w] = v.y;
+        soa[(size_t)(4 * i + 2) * M + w] = v.z;
+        soa[(size_t)(4 * i + 3) * M + w] = v.w;
+    }
+}
+
 struct TagWords {
     uint32_t w[CF_CKPT_TAG_FLOATS];
 };
@@ -329,7 +343,8 @@ struct cf_handle {
     std::vector<uint8_t> model_of_world;
     int cus = 256;
     std::string arch;
-    // device copies
+    // device copies, in one allocation
+    char* tables = nullptr;
     float* par_aos = nullptr;
     float* par_soa = nullptr;
     int32_t* drone_world = nullptr;
@@ -377,7 +392,7 @@ struct cf_mppi {
     cfk::MppiArgs base{};
     cfk::KernelSel ks{};
     float* cost = nullptr;        // [C][N]
-    float* elite_u = nullptr;     // [C][H*4][n_e]
+    float* mean_part = nullptr;   // [C][blocks of 64 elites][4 H + 1]
     int32_t* elite_idx = nullptr; // [C][n_e]
     float* elite_cost = nullptr;  // [C][n_e]
     float* cost_min = nullptr;    // [C]
@@ -697,43 +712,60 @@ cf_status cf_create(const cf_desc* d, cf_handle** out) {
     };
     hipError_t e;
     const size_t M = (size_t)h->M;
-    std::unique_ptr<float[]> aos(new (std::nothrow) float[(size_t)NREC * M]);
-    // the transposed copy serves worlds of a handful of drones, one per lane
-    const bool lanes = h->lane_ok && (double)D / h->M < 32.0;
-    std::unique_ptr<float[]> soa(lanes ? new (std::nothrow) float[(size_t)NREC * M] : nullptr);
-    if (!aos || (lanes && !soa)) return fail(hipErrorOutOfMemory);
+    // The handle's tables in one allocation, filled by one copy: parameter records,
+    // world of each drone, world offsets, gain indices, the status word, the transposed
+    // records (for worlds of a handful of drones, one per lane; many are transposed on
+    // the device) and, uncopied, the work-queue heads.
+    const bool lanes = h->lane_ok && (double)D / h->M < 32.0, host_soa = lanes && M <= 1024;
+    h->n_counters = 4096;
+    size_t end = 0;
+    auto place = [&](size_t bytes) {
+        const size_t at = end;
+        end += (bytes + 255) / 256 * 256;
+        return at;
+    };
+    const size_t rec_bytes = (size_t)NREC * M * sizeof(float), n_dw = (size_t)std::max<int64_t>(D, 1);
+    const size_t o_aos = place(rec_bytes), o_dw = place(n_dw * sizeof(int32_t)), o_off = place((M + 1) * sizeof(int64_t)),
+                 o_gidx = place(M * sizeof(int32_t)), o_flag = place(sizeof(uint32_t));
+    const size_t copied = end;
+    const size_t o_soa = lanes ? place(rec_bytes) : end;
+    const size_t copy_bytes = host_soa ? end : copied;
+    const size_t o_cnt = place((size_t)h->n_counters * sizeof(unsigned));
+    std::unique_ptr<char[]> img(new (std::nothrow) char[copy_bytes]);
+    if (!img) return fail(hipErrorOutOfMemory);
+    float* const aos = (float*)(img.get() + o_aos);
     for (size_t w = 0; w < M; ++w) {
-        cfh::derive_record(d->params + w * CF_NPARAM, aos.get() + w * NREC);
-        cfh::derive_step(models[w], h->dt, aos.get() + w * NREC);
+        cfh::derive_record(d->params + w * CF_NPARAM, aos + w * NREC);
+        cfh::derive_step(models[w], h->dt, aos + w * NREC);
     }
-    // transposed in blocks of worlds, so that both copies stay in cache
-    for (size_t w0 = 0; lanes && w0 < M; w0 += 64)
-        for (int i = 0; i < NREC; ++i)
-            for (size_t w = w0; w < std::min(M, w0 + 64); ++w) soa[(size_t)i * M + w] = aos[w * NREC + i];
-    std::vector<int32_t> dw((size_t)std::max<int64_t>(D, 1));
+    int32_t* const dw = (int32_t*)(img.get() + o_dw);
     for (int w = 0; w < h->M; ++w)
         for (int64_t k = h->offsets[w]; k < h->offsets[w + 1]; ++k) dw[k] = w;
-    if ((e = dalloc(&h->par_aos, M * NREC)) != hipSuccess) return fail(e);
-    if (lanes && (e = dalloc(&h->par_soa, M * NREC)) != hipSuccess) return fail(e);
-    if ((e = dalloc(&h->drone_world, (size_t)std::max<int64_t>(D, 1))) != hipSuccess) return fail(e);
-    if ((e = dalloc(&h->d_offsets, M + 1)) != hipSuccess) return fail(e);
-    if ((e = dalloc(&h->d_gidx, M)) != hipSuccess) return fail(e);
+    std::memcpy(img.get() + o_off, h->offsets.data(), (M + 1) * sizeof(int64_t));
+    std::memcpy(img.get() + o_gidx, gidx.data(), M * sizeof(int32_t));
+    std::memset(img.get() + o_flag, 0, sizeof(uint32_t));
+    if (host_soa) {
+        float* const soa = (float*)(img.get() + o_soa);
+        for (size_t w = 0; w < M; ++w)
+            for (int i = 0; i < NREC; ++i) soa[(size_t)i * M + w] = aos[w * NREC + i];
+    }
+    if ((e = hipMalloc((void**)&h->tables, end)) != hipSuccess) return fail(e);
+    if ((e = hipMemcpy(h->tables, img.get(), copy_bytes, hipMemcpyHostToDevice)) != hipSuccess) return fail(e);
+    h->par_aos = (float*)(h->tables + o_aos);
+    h->drone_world = (int32_t*)(h->tables + o_dw);
+    h->d_offsets = (int64_t*)(h->tables + o_off);
+    h->d_gidx = (int32_t*)(h->tables + o_gidx);
+    h->dflag = (uint32_t*)(h->tables + o_flag);
+    h->counters = (unsigned*)(h->tables + o_cnt);
+    if (lanes) h->par_soa = (float*)(h->tables + o_soa);
+    if (lanes && !host_soa) {
+        hipLaunchKernelGGL(k_transpose_records, dim3((unsigned)((M + 63) / 64)), dim3(64), 0, nullptr, h->par_aos,
+                           (int)M, h->par_soa);
+        if ((e = hipGetLastError()) != hipSuccess || (e = hipStreamSynchronize(nullptr)) != hipSuccess) return fail(e);
+    }
     if ((e = scratch_setup(dev)) != hipSuccess) return fail(e);
     static std::atomic<uint32_t> next_id{1};
     h->id = next_id.fetch_add(1);
-    if ((e = dalloc(&h->dflag, 1)) != hipSuccess) return fail(e);
-    if ((e = hipMemset(h->dflag, 0, sizeof(uint32_t))) != hipSuccess) return fail(e);
-    h->n_counters = 4096;
-    if ((e = dalloc(&h->counters, (size_t)h->n_counters)) != hipSuccess) return fail(e);
-    const size_t rec_bytes = (size_t)NREC * M * sizeof(float);
-    if ((e = hipMemcpy(h->par_aos, aos.get(), rec_bytes, hipMemcpyHostToDevice)) != hipSuccess) return fail(e);
-    if (lanes && (e = hipMemcpy(h->par_soa, soa.get(), rec_bytes, hipMemcpyHostToDevice)) != hipSuccess) return fail(e);
-    if ((e = hipMemcpy(h->drone_world, dw.data(), dw.size() * sizeof(int32_t), hipMemcpyHostToDevice)) != hipSuccess)
-        return fail(e);
-    if ((e = hipMemcpy(h->d_offsets, h->offsets.data(), (M + 1) * sizeof(int64_t), hipMemcpyHostToDevice)) != hipSuccess)
-        return fail(e);
-    if ((e = hipMemcpy(h->d_gidx, gidx.data(), M * sizeof(int32_t), hipMemcpyHostToDevice)) != hipSuccess)
-        return fail(e);
     // streams beyond the caller's are created only where they are used (the
     // auxiliary stream for mixed handles here, the capture stream at the first
     // graph capture): with few hardware queues per process, every extra stream
@@ -762,16 +794,10 @@ cf_status cf_destroy(cf_handle* h) {
     if (h->stream) hipStreamSynchronize(h->stream);
     else hipDeviceSynchronize();
     clear_graphs(h);
-    hipFree(h->par_aos);
-    hipFree(h->par_soa);
-    hipFree(h->drone_world);
-    hipFree(h->d_offsets);
-    hipFree(h->d_gidx);
+    hipFree(h->tables);
     hipFree(h->tiles);
     hipFree(h->ptiles);
     hipFree(h->plist);
-    hipFree(h->counters);
-    hipFree(h->dflag);
     for (DevBuf* b : {&h->ref_tab, &h->seg, &h->ggc, &h->rec, &h->gpart, &h->loss_tmp})
         if (b->p) hipFree(b->p);
     if (h->capture_stream) hipStreamDestroy(h->capture_stream);
@@ -1497,7 +1523,7 @@ cf_status cf_autotune(cf_handle* h, const float* state, const float* cmd, int32_
 
 static void mppi_free(cf_mppi* m) {
     hipFree(m->cost);
-    hipFree(m->elite_u);
+    hipFree(m->mean_part);
     hipFree(m->elite_idx);
     hipFree(m->elite_cost);
     hipFree(m->cost_min);
@@ -1573,7 +1599,7 @@ cf_status cf_mppi_create(cf_handle* h, const cf_mppi_desc* d, cf_mppi** out) {
     const size_t CN = (size_t)a.C * a.N, CE = (size_t)a.C * a.n_e;
     hipError_t e = hipSuccess;
     if (e == hipSuccess) e = dalloc(&m->cost, CN);
-    if (e == hipSuccess) e = dalloc(&m->elite_u, CE * a.H * 4);
+    if (e == hipSuccess) e = dalloc(&m->mean_part, (size_t)a.C * cfk::mppi_mean_blocks(a.n_e) * (4 * (size_t)a.H + 1));
     if (e == hipSuccess) e = dalloc(&m->elite_idx, CE);
     if (e == hipSuccess) e = dalloc(&m->elite_cost, CE);
     if (e == hipSuccess) e = dalloc(&m->cost_min, (size_t)a.C);
@@ -1618,7 +1644,7 @@ cf_status cf_mppi_step(cf_mppi* m, const float* x_now, float* mean, int32_t shif
     a.shift = shift;
     a.iter = iteration;
     a.cost = cost ? cost : m->cost;
-    a.elite_u = m->elite_u;
+    a.mean_part = m->mean_part;
     a.elite_idx = elite_idx ? elite_idx : m->elite_idx;
     a.elite_cost = m->elite_cost;
     a.cost_min = cost_min ? cost_min : m->cost_min;

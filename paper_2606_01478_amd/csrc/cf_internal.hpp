@@ -136,7 +136,7 @@ struct MppiArgs {
     uint64_t seed, iter;
     float* cost;             // [C][N]
     float* eps_out;          // [C][N][H][4] (noise kernel only)
-    float* elite_u;          // scratch [C][H*4][n_e]
+    float* mean_part;        // scratch [C][mppi_mean_blocks(n_e)][4 H + 1]
     int32_t* elite_idx;      // [C][n_e]
     float* elite_cost;       // [C][n_e]
     float* cost_min;         // [C]
@@ -155,6 +155,8 @@ hipError_t launch_rollout_quad(const KernelSel& ks, const RollArgs& a, bool bwd,
 size_t quad_policy_lds(int H, int n_pol);
 bool quad_sums_policy(int H);
 
+// workgroups of 64 elites
+constexpr int mppi_mean_blocks(int n_e) { return (n_e + 63) / 64; }
 hipError_t launch_mppi_rollout(const KernelSel& ks, const MppiArgs& a, hipStream_t s);
 hipError_t launch_mppi_noise(const MppiArgs& a, hipStream_t s);
 hipError_t launch_mppi_select(const MppiArgs& a, hipStream_t s);

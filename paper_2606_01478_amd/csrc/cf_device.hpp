@@ -158,6 +158,32 @@ struct IdParams {
     bool direct;  // c_tau = 0: no thrust dynamics, the commanded thrust acts directly
 };
 
+template <class R>
+__device__ __forceinline__ void load_fp_coef(const R& rec, FpStepCoef& C) {
+    C.k1 = rec(F_K1); C.k2 = rec(F_K2); C.a2r = rec(F_A2R);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        C.tx[i] = rec(F_TX + i); C.ty[i] = rec(F_TY + i); C.tz[i] = rec(F_TZ + i);
+    }
+#pragma unroll
+    for (int i = 0; i < 3; ++i) { C.tr[i] = rec(F_TR + i); C.dj[i] = rec(F_DJ + i); }
+    C.p2 = rec(F_P2); C.p4 = rec(F_P4); C.pf = rec(F_PF);
+    C.q2 = rec(F_Q2); C.q4 = rec(F_Q4); C.qf = rec(F_QF);
+    C.l1 = rec(F_L1); C.l2 = rec(F_L2); C.l4 = rec(F_L4);
+}
+
+__device__ __forceinline__ float in_vector(float s) {
+    float v;
+    asm("v_mov_b32 %0, %1" : "=v"(v) : "s"(s));
+    return v;
+}
+__device__ __forceinline__ void fp_mixing_to_vector(FpStepCoef& C) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) { C.tx[i] = in_vector(C.tx[i]); C.ty[i] = in_vector(C.ty[i]); C.tz[i] = in_vector(C.tz[i]); }
+#pragma unroll
+    for (int i = 0; i < 3; ++i) { C.tr[i] = in_vector(C.tr[i]); C.dj[i] = in_vector(C.dj[i]); }
+}
+
 // AERO = false: the gyroscopic/reaction torques, drag and the general rotor law
 // (distinct acceleration / deceleration coefficients, quadratic term) are
 // compiled out (the flags below become constants and their branches fold away)
@@ -165,18 +191,7 @@ template <bool AERO, class R>
 __device__ __forceinline__ FpParams load_fp(const R& rec) {
     FpParams P;
     P.structured = !AERO;
-    if constexpr (!AERO) {
-        P.st.k1 = rec(F_K1); P.st.k2 = rec(F_K2); P.st.a2r = rec(F_A2R);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            P.st.tx[i] = rec(F_TX + i); P.st.ty[i] = rec(F_TY + i); P.st.tz[i] = rec(F_TZ + i);
-        }
-#pragma unroll
-        for (int i = 0; i < 3; ++i) { P.st.tr[i] = rec(F_TR + i); P.st.dj[i] = rec(F_DJ + i); }
-        P.st.p2 = rec(F_P2); P.st.p4 = rec(F_P4); P.st.pf = rec(F_PF);
-        P.st.q2 = rec(F_Q2); P.st.q4 = rec(F_Q4); P.st.qf = rec(F_QF);
-        P.st.l1 = rec(F_L1); P.st.l2 = rec(F_L2); P.st.l4 = rec(F_L4);
-    }
+    if constexpr (!AERO) load_fp_coef(rec, P.st);
     P.inv_m = rec(D_INV_M);
     P.g = rec(P_GRAVITY);
     P.iJx = rec(D_IJ); P.iJy = rec(D_IJ + 1); P.iJz = rec(D_IJ + 2);
@@ -403,13 +418,19 @@ __device__ __forceinline__ void euler_base(const float* a, EulerBase& b) {
     sincos3(a, b.s0, b.c0);
 }
 
-// sin and cos at N offsets d from the base angles (offset i belongs to angle i % 3)
+// sin and cos at N offsets d from the base angles (offset i belongs to angle i % 3);
+// m: the largest offset that decides (of these, or of all of a step's stages)
 template <int N>
-__device__ __forceinline__ void sincos_off(const float* d, const EulerBase& b, float* s, float* c) {
+__device__ __forceinline__ float largest(const float* d) {
     float m = 0.f;
 #pragma unroll
+    for (int i = 0; i < N; ++i) m = fmaxf(m, fabsf(d[i]));
+    return m;
+}
+template <int N>
+__device__ __forceinline__ void sincos_off(const float* d, float m, const EulerBase& b, float* s, float* c) {
+#pragma unroll
     for (int i = 0; i < N; ++i) {
-        m = fmaxf(m, fabsf(d[i]));
         const float s0 = b.s0[i % 3], c0 = b.c0[i % 3];
         const float d2 = d[i] * d[i];
         const float sd = __builtin_fmaf(d[i] * d2, __builtin_fmaf(d2, 1.f / 120.f, -1.f / 6.f), d[i]);
@@ -427,7 +448,7 @@ __device__ __forceinline__ void sincos_off(const float* d, const EulerBase& b, f
 
 __device__ __forceinline__ void sincos3_near(const float* a, const EulerBase& b, float* s, float* c) {
     const float d[3] = {a[0] - b.a0[0], a[1] - b.a0[1], a[2] - b.a0[2]};
-    sincos_off<3>(d, b, s, c);
+    sincos_off<3>(d, largest<3>(d), b, s, c);
 }
 
 // ---------------------------------------------------------------------------
@@ -1416,9 +1437,8 @@ __device__ __forceinline__ void fp_stage_vjp(const float* q, const float* w, flo
     wb[2] = __builtin_fmaf(-u0, w[1], __builtin_fmaf(-u1, w[0], wb[2]));
 }
 
-template <bool RENORM>
 __device__ __forceinline__ void fp_step_structured_vjp(const float* x, const float* rc, const FpParams& P, float h,
-                                                       const float* yb, float* xb, float* rcb) {
+                                                       int renorm, const float* yb, float* xb, float* rcb) {
     const FpStepCoef& C = P.st;
     const float h2 = 0.5f * h, h4 = 0.25f * h, h6 = h * (1.0f / 6.0f), h12 = 0.5f * h6;
     float W[4][4], q2[4], q3[4], q4[4], w2[3], w3[3], w4[3], kq[4], kw[3], y[7];
@@ -1446,7 +1466,7 @@ __device__ __forceinline__ void fp_step_structured_vjp(const float* x, const flo
     float lq[7];   // rows 3..6: the adjoint of the integrated quaternion
 #pragma unroll
     for (int i = 0; i < 4; ++i) lq[3 + i] = yb[3 + i];
-    if constexpr (RENORM) {
+    if (renorm) {
         quat_rate2(q4, w4, kq);
 #pragma unroll
         for (int i = 0; i < 4; ++i) y[3 + i] = __builtin_fmaf(h12, y[3 + i] + kq[i], q1[i]);
@@ -1542,7 +1562,7 @@ __device__ __forceinline__ void id_step_structured(float* x, float* comp, const 
     IdStages T;
     id_stages(x, u, P, h, T);
     float a[4][3], sn[9], cs[9];
-    sincos_off<9>(T.off, B, sn, cs);
+    sincos_off<9>(T.off, largest<9>(T.off), B, sn, cs);
     id_acc(B.s0, B.c0, T.a[0], P.g, a[0]);
 #pragma unroll
     for (int s = 1; s < 4; ++s) id_acc(sn + 3 * (s - 1), cs + 3 * (s - 1), T.a[s], P.g, a[s]);
@@ -1584,12 +1604,16 @@ __device__ __forceinline__ void id_step_structured_vjp(const float* x, const flo
         xb[i] = yb[i];
         xb[6 + i] = __builtin_fmaf(h, yb[i], lv);
     }
-    float th[4][3], fb[4], sn[9], cs[9];
-    sincos_off<9>(T.off, B, sn, cs);
+    // one stage's sines and cosines at a time: all nine pairs would hold registers
+    float th[4][3], fb[4], sn[3], cs[3];
+    const float m = largest<9>(T.off);
     fb[0] = id_stage_vjp(B.s0, B.c0, T.a[0], g1, th[0]);
+    sincos_off<3>(T.off, m, B, sn, cs);
     fb[1] = id_stage_vjp(sn, cs, T.a[1], g23, th[1]);
-    fb[2] = id_stage_vjp(sn + 3, cs + 3, T.a[2], g23, th[2]);
-    fb[3] = id_stage_vjp(sn + 6, cs + 6, T.a[3], g4, th[3]);
+    sincos_off<3>(T.off + 3, m, B, sn, cs);
+    fb[2] = id_stage_vjp(sn, cs, T.a[2], g23, th[2]);
+    sincos_off<3>(T.off + 6, m, B, sn, cs);
+    fb[3] = id_stage_vjp(sn, cs, T.a[3], g4, th[3]);
 #pragma unroll
     for (int i = 0; i < 3; ++i) {
         const float lw = yb[9 + i], lt = yb[3 + i];
@@ -1734,8 +1758,7 @@ __device__ __forceinline__ void fp_held_vjp(const float* x, const float* rc, con
     const auto vjp = [&](const float* xi, const float* gb, float* xa) { fp_rates_vjp(xi, rc, P, gb, xa, rcb); };
     const auto none = [](const float*, float*) {};
     if (INTEG == RK4 && P.structured) {
-        if (renorm) fp_step_structured_vjp<true>(x, rc, P, dt, yb, xb, rcb);
-        else fp_step_structured_vjp<false>(x, rc, P, dt, yb, xb, rcb);
+        fp_step_structured_vjp(x, rc, P, dt, renorm, yb, xb, rcb);
     } else if (!P.rotor_general && !P.gyro) {
         if (renorm)
             integrate_vjp_fp_linear_rotors<INTEG, true>(x, dt, rc, P.cvu, yb, xb, rcb, rates, vjp, renorm_vjp);

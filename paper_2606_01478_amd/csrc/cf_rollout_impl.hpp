@@ -411,6 +411,10 @@ template <int MODEL, int CTRL, bool AERO, class R>
 __device__ __forceinline__ void load_params(const R& rec, DroneParams& p) {
     if constexpr (MODEL == MODEL_FP) {
         p.fp = load_fp<AERO>(rec);
+        if constexpr (CTRL != CTRL_ROTOR && std::is_same<R, VecRec>::value) p.pid = load_pid(rec, CTRL == CTRL_POSITION);
+        // a uniform record's scalars crowd the scalar registers of the reverse sweep, and
+        // each spilled one costs a VALU slot at every use: keep the mixing in vector ones
+        if constexpr (!AERO && std::is_same<R, ScalarRec>::value) fp_mixing_to_vector(p.fp.st);
     } else {
         p.id = load_id<AERO>(rec);
     }
@@ -419,9 +423,11 @@ __device__ __forceinline__ void load_params(const R& rec, DroneParams& p) {
 // The onboard controller's gains, read right before each use (scalar loads of
 // the world's record through a pointer the optimiser cannot hoist) so that they
 // do not occupy registers through the integration and its reverse sweep.
+// A forward tile (VecRec) has vector registers to spare and holds them.
 template <int MODEL, int CTRL, class R>
 __device__ __forceinline__ void controller_gains(const R& rec, DroneParams& p) {
-    if constexpr (MODEL == MODEL_FP && CTRL != CTRL_ROTOR) p.pid = load_pid(laundered(rec), CTRL == CTRL_POSITION);
+    if constexpr (MODEL == MODEL_FP && CTRL != CTRL_ROTOR && !std::is_same<R, VecRec>::value)
+        p.pid = load_pid(laundered(rec), CTRL == CTRL_POSITION);
 }
 
 // one step; rc holds the first-principles rotor commands across steps, the
@@ -506,6 +512,8 @@ __device__ __forceinline__ void rollout_fwd_drone(const R& rec, const RollArgs& 
     EulerBase B;
     const bool rew = EXT && a.has_obj && a.obj_kind == 1;
     float uprev[4] = {0.f, 0.f, 0.f, 0.f};   // reward: the previous applied command
+    int left = a.K;                          // steps to the next checkpoint
+    float* ck = a.ckpt;
     if (rew) hover_action<MODEL, CTRL>(p, uprev);
     for (int t = 0; t < a.T; ++t) {
         float u[4], ev[13], unext[4];
@@ -547,7 +555,11 @@ __device__ __forceinline__ void rollout_fwd_drone(const R& rec, const RollArgs& 
             }
         }
         const int tn = t + 1;
-        if (a.ckpt && tn < a.T && (tn % a.K) == 0) store_state<MODEL, S>(a.ckpt + (size_t)(tn / a.K) * SD, D, d, x, p);
+        if (--left == 0) {
+            left = a.K;
+            ck += SD;
+            if (a.ckpt && tn < a.T) store_state<MODEL, S>(ck, D, d, x, p);
+        }
         if (a.traj) store_state<MODEL, S>(a.traj + (size_t)tn * SD, D, d, x, p);
 #pragma unroll
         for (int i = 0; i < 4; ++i) ubar[i] = unext[i];
@@ -644,9 +656,10 @@ __device__ __forceinline__ void rollout_bwd_drone(const R& rec, const RollArgs& 
             if constexpr (HAS_CTRL) {
                 // a segment that starts inside a block (period longer than the
                 // checkpoint interval) starts with that block's held commands
-                if (t0 % n_c != 0)
+                if (t0 % n_c != 0) {
                     controller_gains<MODEL, CTRL>(rec, p);
                     block_commands<MODEL, CTRL, S>(a, p, G, gl, gs, off, f_hover, D, d, SD, t0 - t0 % n_c, t0, rcf);
+                }
             }
             for (int j = 0; j < n_re; ++j) {
                 float u[4], ev[13], ubar[4];
@@ -721,9 +734,10 @@ __device__ __forceinline__ void rollout_bwd_drone(const R& rec, const RollArgs& 
                 if (n_c > 1) {
                     held = true;
                     const int tb = t - t % n_c;
-                    if (t == a.T - 1 || (t + 1) % n_c == 0)   // first visit of this block
+                    if (t == a.T - 1 || (t + 1) % n_c == 0) {   // first visit of this block
                         controller_gains<MODEL, CTRL>(rec, p);
                         block_commands<MODEL, CTRL, S>(a, p, G, gl, gs, off, f_hover, D, d, SD, tb, t0, rch);
+                    }
                     fp_held_vjp<INTEG>(xc, rch, p.fp, a.dt, a.renorm, lam, xb, rcb);
                     if constexpr (S > S_FP) {
 #pragma unroll
@@ -817,19 +831,14 @@ __device__ __forceinline__ void rollout_bwd_drone(const R& rec, const RollArgs& 
                     for (int i = 0; i < 4; ++i) s2 += G[i * 13 + j] * ob[i];
                     xb[j] += s2;
                 }
-                float gv[NG];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-#pragma unroll
-                    for (int j = 0; j < 13; ++j) gv[i * 13 + j] = ob[i] * ev[j];
-                }
 #pragma unroll
                 for (int q = 0; q < NG / 4; ++q) {
+                    const int k = 4 * q;
                     float4 s4 = gq[q * gs];
-                    s4.x += gv[4 * q];
-                    s4.y += gv[4 * q + 1];
-                    s4.z += gv[4 * q + 2];
-                    s4.w += gv[4 * q + 3];
+                    s4.x = fmaf(ob[k / 13], ev[k % 13], s4.x);
+                    s4.y = fmaf(ob[(k + 1) / 13], ev[(k + 1) % 13], s4.y);
+                    s4.z = fmaf(ob[(k + 2) / 13], ev[(k + 2) % 13], s4.z);
+                    s4.w = fmaf(ob[(k + 3) / 13], ev[(k + 3) % 13], s4.w);
                     gq[q * gs] = s4;
                 }
             }
@@ -951,8 +960,13 @@ __global__ __launch_bounds__(256) void k_rollout_lane(RollArgs a, int S_h) {
     else rollout_drone<BWD, MODEL_ID, CTRL, INTEG, AERO, EXT>(rec, a, d, w, S_h, G, gl, gs);
 }
 
+// Identified drones are held to four waves per SIMD (128 registers, a few spilled):
+// their adjoint shares the compute units with the first-principles one, whose 244
+// registers leave room for no wider wave (118 000 uneven drones, 250 steps, both
+// models, forward and adjoint: 3047 us, unbounded 3125 us).
 template <bool BWD, int MODELS, int CTRL, int INTEG, bool AERO, bool EXT>
-__global__ __launch_bounds__(256) void k_rollout_tile(RollArgs a, const int4* __restrict__ tiles, int S_h) {
+__global__ __launch_bounds__(256, (MODELS == MS_ID && !EXT && !AERO) ? 4 : 1) void k_rollout_tile(
+    RollArgs a, const int4* __restrict__ tiles, int S_h) {
     rollout_priority();
     const int4 td = tiles[blockIdx.x];
     const int w = __builtin_amdgcn_readfirstlane(td.x);
@@ -973,7 +987,7 @@ __global__ __launch_bounds__(256) void k_rollout_tile(RollArgs a, const int4* __
         G = sG;
     }
     if ((int)threadIdx.x >= cnt) return;
-    using Rec = typename std::conditional<BWD, ScalarRec, AosRec>::type;
+    using Rec = typename std::conditional<BWD, ScalarRec, typename std::conditional<MODELS == MS_FP, VecRec, AosRec>::type>::type;
     const Rec rec{a.par_aos + (size_t)w * NREC};
     const size_t d = (size_t)d0 + threadIdx.x;
     if constexpr (BWD) {

@@ -81,6 +81,43 @@ __device__ __forceinline__ ScalarRec laundered(ScalarRec r) {
     return r;
 }
 
+// A world per lane with the fields that a step reads (its coefficients, D_STEP on,
+// and the controller's gains) in the lane's own LDS columns, for kernels whose
+// registers are full: read where they are used (laundered below), a field costs an
+// LDS read of two cycles instead of a register held through the sweep or a load
+// from memory. One wave per workgroup.
+template <int CTRL>
+struct LaneLds {
+    static constexpr int LANES = 64;
+    static constexpr int COEFS = F_L4 + 1 - D_STEP;
+    static constexpr int GAINS = P_ALLOC + 16 - P_ANG_KP;      // attitude gains to the allocation
+    static constexpr int COLS = COEFS + (CTRL == CTRL_ROTOR ? 0 : GAINS) + (CTRL == CTRL_POSITION ? 14 : 0);
+    SoaRec soa;
+    __attribute__((address_space(3))) float* col;
+    // the column of a field, or -1 (constant folded: fields are compile-time)
+    static __device__ __forceinline__ constexpr int column(int i) {
+        if (i >= D_STEP && i < D_STEP + COEFS) return i - D_STEP;
+        if (CTRL != CTRL_ROTOR && i >= P_ANG_KP && i < P_ANG_KP + GAINS) return COEFS + i - P_ANG_KP;
+        if (CTRL == CTRL_POSITION && i >= P_POS_KP && i < P_POS_KP + 12) return COEFS + GAINS + i - P_POS_KP;
+        if (CTRL == CTRL_POSITION && (i == P_MASS || i == P_GRAVITY)) return COEFS + GAINS + 12 + i;
+        return -1;
+    }
+    __device__ __forceinline__ LaneLds(const SoaRec& s, float* cols) : soa(s) {
+        col = (__attribute__((address_space(3))) float*)cols + threadIdx.x;
+#pragma unroll
+        for (int i = 0; i < NREC; ++i)
+            if (column(i) >= 0) col[column(i) * LANES] = soa(i);
+    }
+    __device__ __forceinline__ float operator()(int i) const {
+        return column(i) >= 0 ? col[column(i) * LANES] : soa(i);
+    }
+};
+template <int CTRL>
+__device__ __forceinline__ LaneLds<CTRL> laundered(LaneLds<CTRL> r) {
+    asm volatile("" : "+v"(r.col));
+    return r;
+}
+
 // a world record whose address differs across the lanes of a wave (a packed
 // tile across a world boundary): per-lane vector loads
 struct LaneRec {
@@ -1773,33 +1810,37 @@ __device__ __forceinline__ void fp_held_vjp(const float* x, const float* rc, con
 
 // VJP of fp_step at (x, u) with the controller evaluated in this step: yb =
 // adjoint of the new state (S components), writes xb (S) and accumulates ub (4).
-template <int CTRL, int INTEG>
-__device__ __forceinline__ void fp_step_vjp(const float* x, const float* u, const FpParams& P,
-                                            const PidParams& C, float dt, float dtc, float inv_dtc, int renorm,
-                                            const float* yb, float* xb, float* ub) {
+// gains() reads the controller's gains, coefs(P) the step's coefficients; swept() is
+// called after the integration's reverse sweep, before the controller's VJP.
+template <int CTRL, int INTEG, class Gains, class Coefs, class Swept>
+__device__ __forceinline__ void fp_step_vjp(const float* x, const float* u, FpParams& P, const Gains& gains,
+                                            const Coefs& coefs, const Swept& swept, float dt, float dtc, float inv_dtc,
+                                            int renorm, const float* yb, float* xb, float* ub) {
     float rc[4], cs[8];
     PidTrace tr;
     PosTrace pt;
     if constexpr (CTRL == CTRL_PID) {
-        pid_forward(x, u, P, C, dtc, inv_dtc, rc, cs, tr);
+        pid_forward(x, u, P, gains(), dtc, inv_dtc, rc, cs, tr);
     } else if constexpr (CTRL == CTRL_TORQUE) {
-        allocate(u, P, C, rc, tr);
+        allocate(u, P, gains(), rc, tr);
     } else if constexpr (CTRL == CTRL_POSITION) {
-        pos_forward(x, u, P, C, rc, tr, pt);
+        pos_forward(x, u, P, gains(), rc, tr, pt);
     } else {
 #pragma unroll
         for (int i = 0; i < 4; ++i) rc[i] = u[i] - P.wr;
     }
     float rcb[4] = {0.f, 0.f, 0.f, 0.f};
+    coefs(P);
     fp_held_vjp<INTEG>(x, rc, P, dt, renorm, yb, xb, rcb);
+    swept();
     if constexpr (CTRL == CTRL_PID) {
 #pragma unroll
         for (int i = S_FP; i < S_PID; ++i) xb[i] = 0.f;
-        pid_vjp(x, P, C, dtc, inv_dtc, tr, rcb, yb + S_FP, xb, ub);
+        pid_vjp(x, P, gains(), dtc, inv_dtc, tr, rcb, yb + S_FP, xb, ub);
     } else if constexpr (CTRL == CTRL_TORQUE) {
-        allocate_vjp(C, tr, rcb, ub);
+        allocate_vjp(gains(), tr, rcb, ub);
     } else if constexpr (CTRL == CTRL_POSITION) {
-        pos_vjp(x, C, tr, pt, rcb, xb, ub);
+        pos_vjp(x, gains(), tr, pt, rcb, xb, ub);
     } else {
 #pragma unroll
         for (int i = 0; i < 4; ++i) ub[i] += rcb[i];

@@ -23,6 +23,50 @@ namespace cfk {
 
 constexpr int NG = 52;  // 4 x 13 gain entries
 
+// A drone as its workgroup's first one (uniform) and the lane's byte offset from it in
+// a row of 4-byte entries: every row access then takes a scalar base and a 32-bit lane
+// offset, where a drone number of 64 bits per lane costs an address addition per row
+// (in vector registers, with the row offsets spilled from the scalar ones). Loss and
+// gradient of 118 000 uneven drones, 250 steps: 3050 -> 2520 us; of 262 144 worlds of
+// one drone, 10 steps: 325 -> 300 us.
+struct DroneAt {
+    size_t first;
+    uint32_t byte;
+};
+__device__ __forceinline__ DroneAt drone_at(size_t first) { return DroneAt{first, threadIdx.x * 4u}; }
+template <class T>
+using global_ptr = __attribute__((address_space(1))) T*;
+// (a row's base is uniform; said so, it stays scalar: left to itself the compiler adds
+// the lane's offset first and the row's to that, in vector registers)
+template <class T>
+__device__ __forceinline__ global_ptr<T> row_base(T* p) {
+    const uint64_t b = (uint64_t)p;
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)b), hi = __builtin_amdgcn_readfirstlane((uint32_t)(b >> 32));
+    return (global_ptr<T>)((uint64_t)hi << 32 | lo);
+}
+template <class T>
+__device__ __forceinline__ global_ptr<T> next_row(global_ptr<T> p, size_t D) {
+    p += D;
+    asm("" : "+s"(p));
+    return p;
+}
+template <class T>
+__device__ __forceinline__ global_ptr<T> lane_of(global_ptr<T> row, uint32_t byte) {
+    static_assert(sizeof(T) == 4, "rows of 4-byte entries");
+    using Byte = typename std::conditional<std::is_const<T>::value, const char, char>::type;
+    return (global_ptr<T>)((global_ptr<Byte>)row + byte);
+}
+// (the offset's extension to 64 bits has to stand beside its use to become the load's
+// 32-bit offset field)
+__device__ __forceinline__ uint32_t here(uint32_t byte) {
+    asm volatile("" : "+v"(byte));
+    return byte;
+}
+template <class T>
+__device__ __forceinline__ __attribute__((address_space(1))) T& at(T* p, size_t row, const DroneAt& d) {
+    return *lane_of(row_base(p + row + d.first), here(d.byte));
+}
+
 // The reference table is the same for every drone and never written while a
 // rollout runs: its rows are read through the constant address space, i.e.
 // with scalar loads into the wave's scalar registers.
@@ -45,15 +89,15 @@ struct RefLane {
 };
 
 template <bool EXT>
-__device__ __forceinline__ RefLane ref_lane(const RollArgs& a, size_t D, size_t d) {
+__device__ __forceinline__ RefLane ref_lane(const RollArgs& a, size_t D, const DroneAt& d) {
     RefLane r{{0.f, 0.f, 0.f}, 1.f, 0.f, 1.f, 0.f};
     if (a.has_obj && a.ref_off) {
 #pragma unroll
-        for (int j = 0; j < 3; ++j) r.off[j] = a.ref_off[j * D + d];
+        for (int j = 0; j < 3; ++j) r.off[j] = at(a.ref_off, j * D, d);
     }
     if constexpr (EXT) {
         if (a.has_obj && a.ref_shift) {
-            sincosf(a.ref_w * a.ref_shift[d], &r.s1, &r.c1);
+            sincosf(a.ref_w * at(a.ref_shift, 0, d), &r.s1, &r.c1);
             r.c2 = r.c1 * r.c1 - r.s1 * r.s1;
             r.s2 = 2.f * r.s1 * r.c1;
         }
@@ -126,10 +170,10 @@ __device__ __forceinline__ void ref_state(const RollArgs& a, int t, const RefLan
 }
 
 // per-step command ubar_t of drone d
-__device__ __forceinline__ void load_cmd(const RollArgs& a, int t, size_t d, float* ub) {
+__device__ __forceinline__ void load_cmd(const RollArgs& a, int t, const DroneAt& d, float* ub) {
     const size_t D = (size_t)a.D;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) ub[i] = a.cmds[((size_t)t * 4 + i) * D + d];
+    for (int i = 0; i < 4; ++i) ub[i] = at(a.cmds, ((size_t)t * 4 + i) * D, d);
 }
 
 // u += o, or u += s * tanh(o) for a squashed policy output (extended kernels):
@@ -430,6 +474,12 @@ __device__ __forceinline__ void controller_gains(const R& rec, DroneParams& p) {
         p.pid = load_pid(laundered(rec), CTRL == CTRL_POSITION);
 }
 
+// The step's coefficients, read again where a world per lane keeps them in LDS
+template <int MODEL, int CTRL, class R>
+__device__ __forceinline__ void step_coefs(const R& rec, FpParams& P) {
+    if constexpr (MODEL == MODEL_FP && std::is_same<R, LaneLds<CTRL>>::value) load_fp_coef(laundered(rec), P.st);
+}
+
 // one step; rc holds the first-principles rotor commands across steps, the
 // onboard controller runs when ctrl_now; n counts the steps since the run began and
 // B carries the identified model's start angles' sines and cosines
@@ -445,24 +495,35 @@ __device__ __forceinline__ void model_step(float* x, float* comp, const float* u
 }
 
 // VJP of a step whose controller (if any) runs every step
-template <int MODEL, int CTRL, int INTEG>
-__device__ __forceinline__ void model_step_vjp(const float* x, const float* u, const DroneParams& p,
-                                               const RollArgs& a, const float* yb, float* xb, float* ub) {
-    if constexpr (MODEL == MODEL_FP)
-        fp_step_vjp<CTRL, INTEG>(x, u, p.fp, p.pid, a.dt, a.dtc, a.inv_dtc, a.renorm, yb, xb, ub);
-    else
+// (the gains are read for the controller and again for its VJP, so that they hold no
+// registers through the reverse sweep of the integration between the two)
+template <int MODEL, int CTRL, int INTEG, class R, class Swept>
+__device__ __forceinline__ void model_step_vjp(const R& rec, const Swept& swept, const float* x, const float* u,
+                                               DroneParams& p, const RollArgs& a, const float* yb, float* xb,
+                                               float* ub) {
+    if constexpr (MODEL == MODEL_FP) {
+        fp_step_vjp<CTRL, INTEG>(
+            x, u, p.fp, [&]() { return load_pid(laundered(rec), CTRL == CTRL_POSITION); },
+            [&](FpParams& P) { step_coefs<MODEL, CTRL>(rec, P); }, swept, a.dt, a.dtc, a.inv_dtc, a.renorm, yb, xb, ub);
+    } else {
         id_step_vjp<INTEG>(x, u, p.id, a.dt, yb, xb, ub);
+        swept();
+    }
 }
 
 template <int N>
-__device__ __forceinline__ void store_rows(float* dst, size_t D, size_t d, const float* x) {
+__device__ __forceinline__ void store_rows(float* dst, size_t D, const DroneAt& d, const float* x) {
+    auto row = row_base(dst + d.first);
+    const uint32_t byte = here(d.byte);
 #pragma unroll
-    for (int i = 0; i < N; ++i) dst[i * D + d] = x[i];
+    for (int i = 0; i < N; ++i, row = next_row(row, D)) *lane_of(row, byte) = x[i];
 }
 template <int N>
-__device__ __forceinline__ void load_rows(const float* src, size_t D, size_t d, float* x) {
+__device__ __forceinline__ void load_rows(const float* src, size_t D, const DroneAt& d, float* x) {
+    auto row = row_base(src + d.first);
+    const uint32_t byte = here(d.byte);
 #pragma unroll
-    for (int i = 0; i < N; ++i) x[i] = src[i * D + d];
+    for (int i = 0; i < N; ++i, row = next_row(row, D)) x[i] = *lane_of(row, byte);
 }
 
 // states in caller-visible buffers (x0, checkpoints, trajectory, x_T) hold
@@ -473,7 +534,7 @@ __device__ __forceinline__ void to_dev(float* x, const DroneParams& p) {
     if constexpr (MODEL == MODEL_FP) rotors_to_dev(x, p.fp);
 }
 template <int MODEL, int N>
-__device__ __forceinline__ void store_state(float* dst, size_t D, size_t d, const float* x, const DroneParams& p) {
+__device__ __forceinline__ void store_state(float* dst, size_t D, const DroneAt& d, const float* x, const DroneParams& p) {
     if constexpr (MODEL == MODEL_FP) {
         float y[N];
 #pragma unroll
@@ -488,7 +549,7 @@ __device__ __forceinline__ void store_state(float* dst, size_t D, size_t d, cons
 // ---------------------------------------------------------------------------
 // forward rollout of one drone
 template <int MODEL, int CTRL, int INTEG, bool AERO, bool EXT, class R>
-__device__ __forceinline__ void rollout_fwd_drone(const R& rec, const RollArgs& a, size_t d, int w, int S_h,
+__device__ __forceinline__ void rollout_fwd_drone(const R& rec, const RollArgs& a, const DroneAt& d, int w, int S_h,
                                                   const float* G, float* hc, int ws) {
     constexpr int S = ModelTraits<MODEL, CTRL>::S;
     const size_t D = (size_t)a.D;
@@ -531,7 +592,7 @@ __device__ __forceinline__ void rollout_fwd_drone(const R& rec, const RollArgs& 
             // kept for the backward, which needs the neighbours of every command
             if (a.ubuf) {
 #pragma unroll
-                for (int i = 0; i < 4; ++i) a.ubuf[((size_t)t * 4 + i) * D + d] = u[i];
+                for (int i = 0; i < 4; ++i) at(a.ubuf, ((size_t)t * 4 + i) * D, d) = u[i];
             }
         } else if (a.has_obj) {
             loss += a.w_u * (u[0] * u[0] + u[1] * u[1] + u[2] * u[2] + u[3] * u[3]);
@@ -565,7 +626,7 @@ __device__ __forceinline__ void rollout_fwd_drone(const R& rec, const RollArgs& 
         for (int i = 0; i < 4; ++i) ubar[i] = unext[i];
     }
     if (a.xT) store_state<MODEL, S>(a.xT, D, d, x, p);
-    if (a.loss) a.loss[d] = loss;
+    if (a.loss) at(a.loss, 0, d) = loss;
     if (a.nonfinite) {
         bool bad = false;
 #pragma unroll
@@ -579,7 +640,7 @@ __device__ __forceinline__ void rollout_fwd_drone(const R& rec, const RollArgs& 
 // else slot tb - t0 of the current segment) under the command applied there.
 template <int MODEL, int CTRL, int S>
 __device__ __forceinline__ void block_commands(const RollArgs& a, const DroneParams& p, const float* G, float* hc,
-                                               int ws, const RefLane& off, float f_hover, size_t D, size_t d,
+                                               int ws, const RefLane& off, float f_hover, size_t D, const DroneAt& d,
                                                size_t SD, int tb, int t0, float* rc) {
     float xs[S], ubs[4], us[4], evs[13], cs[8];
     if (tb % a.K == 0) {
@@ -596,7 +657,7 @@ __device__ __forceinline__ void block_commands(const RollArgs& a, const DronePar
 // ---------------------------------------------------------------------------
 // adjoint of one drone's rollout
 template <int MODEL, int CTRL, int INTEG, bool AERO, bool EXT, class R>
-__device__ __forceinline__ void rollout_bwd_drone(const R& rec, const RollArgs& a, size_t d, int w, int S_h,
+__device__ __forceinline__ void rollout_bwd_drone(const R& rec, const RollArgs& a, const DroneAt& d, int w, int S_h,
                                                   const float* G, float* gl, int gs) {
     constexpr int S = ModelTraits<MODEL, CTRL>::S;
     const size_t D = (size_t)a.D;
@@ -605,7 +666,7 @@ __device__ __forceinline__ void rollout_bwd_drone(const R& rec, const RollArgs& 
     load_params<MODEL, CTRL, AERO>(rec, p);
     const float f_hover = (MODEL == MODEL_ID) ? p.id.f_hover : 0.f;
     const RefLane off = ref_lane<EXT>(a, D, d);
-    const float seed = a.dloss ? a.dloss[d] : 1.f;
+    const float seed = a.dloss ? at(a.dloss, 0, d) : 1.f;
     const float two_seed = 2.f * seed;
     float lam[S];
 #pragma unroll
@@ -666,6 +727,7 @@ __device__ __forceinline__ void rollout_bwd_drone(const R& rec, const RollArgs& 
                 load_cmd(a, t0 + j, d, ubar);
                 apply_feedback<MODEL, EXT>(a, G, gl, gs, x, t0 + j, off, f_hover, ubar, u, ev);
                 controller_gains<MODEL, CTRL>(rec, p);
+                if constexpr (MODEL == MODEL_FP) step_coefs<MODEL, CTRL>(rec, p.fp);
                 model_step<MODEL, CTRL, INTEG>(x, comp, u, p, a, rcf, (t0 + j) % n_c == 0, B, j);
                 if (j + 1 < t1 - t0 || rew) store_rows<S>(a.seg + (size_t)(j + 1) * SD, D, d, x);
             }
@@ -691,17 +753,23 @@ __device__ __forceinline__ void rollout_bwd_drone(const R& rec, const RollArgs& 
             // issue the loads of step t - 1: a slot or the checkpoint of this
             // segment, or, with a checkpoint every step, the previous checkpoint
             have_q = false;
-            if (t > t0) {
-                q_ck = !(t - 1 > t0);
-                load_rows<S>(q_ck ? ck : a.seg + (size_t)(t - 1 - t0) * SD, D, d, xq);
-                load_cmd(a, t - 1, d, uq);
-                have_q = true;
-            } else if (a.K == 1 && s > 0) {
-                q_ck = true;
-                load_rows<S>(a.ckpt_in + (size_t)(s - 1) * SD, D, d, xq);
-                load_cmd(a, t - 1, d, uq);
-                have_q = true;
-            }
+            const auto load_ahead = [&]() {
+                if (t > t0) {
+                    q_ck = !(t - 1 > t0);
+                    load_rows<S>(q_ck ? ck : a.seg + (size_t)(t - 1 - t0) * SD, D, d, xq);
+                    load_cmd(a, t - 1, d, uq);
+                    have_q = true;
+                } else if (a.K == 1 && s > 0) {
+                    q_ck = true;
+                    load_rows<S>(a.ckpt_in + (size_t)(s - 1) * SD, D, d, xq);
+                    load_cmd(a, t - 1, d, uq);
+                    have_q = true;
+                }
+            };
+            // A kernel with two waves per SIMD only if the loads' registers are free
+            // during the sweep issues them after it; the other wave fills the wait.
+            constexpr bool LATE = std::is_same<R, LaneLds<CTRL>>::value;
+            if constexpr (!LATE) load_ahead();
             if (a.has_obj) {
                 float pr[3];
                 ref_pos<EXT>(a, t + 1, off, pr);
@@ -712,7 +780,7 @@ __device__ __forceinline__ void rollout_bwd_drone(const R& rec, const RollArgs& 
                                                                    : a.ckpt_in + (size_t)(s + 1) * SD;
                     float an[4];
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) an[j] = (MODEL == MODEL_FP || j < 2) ? nx[(3 + j) * D + d] : 0.f;
+                    for (int j = 0; j < 4; ++j) an[j] = (MODEL == MODEL_FP || j < 2) ? at(nx, (3 + j) * D, d) : 0.f;
                     const float e0 = pn[0] - pr[0], e1 = pn[1] - pr[1], e2 = pn[2] - pr[2];
                     const float dn = sqrtf(e0 * e0 + e1 * e1 + e2 * e2);
                     const float g = dn > 0.f ? seed * 2.f * expf(-2.f * dn) / dn : 0.f;
@@ -753,8 +821,7 @@ __device__ __forceinline__ void rollout_bwd_drone(const R& rec, const RollArgs& 
                 }
             }
             if (!held) {
-                controller_gains<MODEL, CTRL>(rec, p);
-                model_step_vjp<MODEL, CTRL, INTEG>(xc, u, p, a, lam, xb, ub);
+                model_step_vjp<MODEL, CTRL, INTEG>(rec, [&]() { if constexpr (LATE) load_ahead(); }, xc, u, p, a, lam, xb, ub);
             }
             if (rew) {
                 // action terms: (u_t - u_hover)^2, (u_t - u_{t-1})^2 and, from the
@@ -763,8 +830,8 @@ __device__ __forceinline__ void rollout_bwd_drone(const R& rec, const RollArgs& 
                 hover_action<MODEL, CTRL>(p, ah);
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    up[i] = t > 0 ? a.ubuf[((size_t)(t - 1) * 4 + i) * D + d] : ah[i];
-                    un[i] = t + 1 < a.T ? a.ubuf[((size_t)(t + 1) * 4 + i) * D + d] : u[i];
+                    up[i] = t > 0 ? at(a.ubuf, ((size_t)(t - 1) * 4 + i) * D, d) : ah[i];
+                    un[i] = t + 1 < a.T ? at(a.ubuf, ((size_t)(t + 1) * 4 + i) * D, d) : u[i];
                 }
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
@@ -778,7 +845,7 @@ __device__ __forceinline__ void rollout_bwd_drone(const R& rec, const RollArgs& 
             }
             if (a.g_cmds) {
 #pragma unroll
-                for (int i = 0; i < 4; ++i) a.g_cmds[((size_t)t * 4 + i) * D + d] = ub[i];
+                for (int i = 0; i < 4; ++i) at(a.g_cmds, ((size_t)t * 4 + i) * D, d) = ub[i];
             }
             if (G && mlp) {
                 // the policy's activations at e_t (recomputed: a controller block's
@@ -795,17 +862,17 @@ __device__ __forceinline__ void rollout_bwd_drone(const R& rec, const RollArgs& 
 #pragma unroll
                 for (int j = 0; j < 13; ++j) xb[j] += eb[j];
                 if (a.mlp_rec) {
-                    const size_t TD = (size_t)a.T * D, base = (size_t)t * D + d;
+                    const size_t TD = (size_t)a.T * D, base = (size_t)t * D;
 #pragma unroll
-                    for (int j = 0; j < 13; ++j) a.mlp_rec[j * TD + base] = ev[j];
+                    for (int j = 0; j < 13; ++j) at(a.mlp_rec, j * TD + base, d) = ev[j];
                     for (int k = 0; k < H; ++k) {
-                        a.mlp_rec[(13 + k) * TD + base] = gl[k * gs];                  // h1
-                        a.mlp_rec[(13 + H + k) * TD + base] = gl[(H + k) * gs];        // h2
-                        a.mlp_rec[(13 + 2 * H + k) * TD + base] = gl[(3 * H + k) * gs];  // dz1
-                        a.mlp_rec[(13 + 3 * H + k) * TD + base] = gl[(2 * H + k) * gs];  // dz2
+                        at(a.mlp_rec, (13 + k) * TD + base, d) = gl[k * gs];                  // h1
+                        at(a.mlp_rec, (13 + H + k) * TD + base, d) = gl[(H + k) * gs];        // h2
+                        at(a.mlp_rec, (13 + 2 * H + k) * TD + base, d) = gl[(3 * H + k) * gs];  // dz1
+                        at(a.mlp_rec, (13 + 3 * H + k) * TD + base, d) = gl[(2 * H + k) * gs];  // dz2
                     }
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) a.mlp_rec[(13 + 4 * H + i) * TD + base] = ob[i];
+                    for (int i = 0; i < 4; ++i) at(a.mlp_rec, (13 + 4 * H + i) * TD + base, d) = ob[i];
                 }
             } else if (G) {
                 float ob[4];
@@ -858,21 +925,21 @@ __device__ __forceinline__ void rollout_bwd_drone(const R& rec, const RollArgs& 
         store_rows<S>(a.g_x0, D, d, lam);
         // rows the drone's model does not use (identified drones of a handle with
         // more rows) do not affect the loss
-        for (int i = S; i < S_h; ++i) a.g_x0[(size_t)i * D + d] = 0.f;
+        for (int i = S; i < S_h; ++i) at(a.g_x0, (size_t)i * D, d) = 0.f;
     }
     if (a.ggc) {
         if (G && !mlp) {
 #pragma unroll
             for (int q = 0; q < NG / 4; ++q) {
                 const float4 s4 = gq[q * gs];
-                a.ggc[(4 * q) * D + d] = s4.x;
-                a.ggc[(4 * q + 1) * D + d] = s4.y;
-                a.ggc[(4 * q + 2) * D + d] = s4.z;
-                a.ggc[(4 * q + 3) * D + d] = s4.w;
+                at(a.ggc, (4 * q) * D, d) = s4.x;
+                at(a.ggc, (4 * q + 1) * D, d) = s4.y;
+                at(a.ggc, (4 * q + 2) * D, d) = s4.z;
+                at(a.ggc, (4 * q + 3) * D, d) = s4.w;
             }
         } else {
 #pragma unroll
-            for (int i = 0; i < NG; ++i) a.ggc[i * D + d] = 0.f;
+            for (int i = 0; i < NG; ++i) at(a.ggc, i * D, d) = 0.f;
         }
     }
 }
@@ -887,15 +954,15 @@ __device__ __forceinline__ bool ckpt_tag_intact(const RollArgs& a) {
     return ok;
 }
 
-__device__ __forceinline__ void poison_gradients(const RollArgs& a, size_t d) {
+__device__ __forceinline__ void poison_gradients(const RollArgs& a, const DroneAt& d) {
     const size_t D = (size_t)a.D;
     const float nan = __builtin_nanf("");
     if (a.g_cmds)
-        for (size_t i = 0; i < (size_t)a.T * 4; ++i) a.g_cmds[i * D + d] = nan;
+        for (size_t i = 0; i < (size_t)a.T * 4; ++i) at(a.g_cmds, i * D, d) = nan;
     if (a.g_x0)
-        for (int i = 0; i < a.S_h; ++i) a.g_x0[(size_t)i * D + d] = nan;
+        for (int i = 0; i < a.S_h; ++i) at(a.g_x0, (size_t)i * D, d) = nan;
     if (a.ggc)
-        for (int i = 0; i < NG; ++i) a.ggc[(size_t)i * D + d] = nan;
+        for (int i = 0; i < NG; ++i) at(a.ggc, (size_t)i * D, d) = nan;
     atomicOr(a.dflag, 1u);
 }
 
@@ -909,7 +976,7 @@ __device__ __forceinline__ void poison_gradients(const RollArgs& a, size_t d) {
 __device__ __forceinline__ void rollout_priority() { __builtin_amdgcn_s_setprio(3); }
 
 template <bool BWD, int MODEL, int CTRL, int INTEG, bool AERO, bool EXT, class R>
-__device__ __forceinline__ void rollout_drone(const R& rec, const RollArgs& a, size_t d, int w, int S_h,
+__device__ __forceinline__ void rollout_drone(const R& rec, const RollArgs& a, const DroneAt& d, int w, int S_h,
                                               const float* G, float* gl, int gs) {
     if constexpr (BWD) {
         rollout_bwd_drone<MODEL, CTRL, INTEG, AERO, EXT>(rec, a, d, w, S_h, G, gl, gs);
@@ -938,25 +1005,41 @@ __device__ __forceinline__ float* stage_policies(const RollArgs& a, float* lds) 
     return lds + threadIdx.x;
 }
 
+// whether a lane kernel keeps its worlds' coefficients and gains in LDS, one wave a
+// workgroup: the reduced adjoints with an onboard controller, which would otherwise take
+// more than 256 registers and leave one wave per SIMD, where an instruction issues every
+// five cycles instead of every 2.6 (262 144 worlds, 10 steps, loss and gradient: 300 us
+// with everything in registers, 268 us so)
 template <bool BWD, int MODELS, int CTRL, int INTEG, bool AERO, bool EXT>
-__global__ __launch_bounds__(256) void k_rollout_lane(RollArgs a, int S_h) {
+constexpr bool lane_in_lds() {
+    return BWD && MODELS == MS_FP && CTRL != CTRL_ROTOR && INTEG == RK4 && !AERO && !EXT;
+}
+
+template <bool BWD, int MODELS, int CTRL, int INTEG, bool AERO, bool EXT>
+__global__ __launch_bounds__(256, (lane_in_lds<BWD, MODELS, CTRL, INTEG, AERO, EXT>() ? 2 : 1)) void k_rollout_lane(
+    RollArgs a, int S_h) {
     rollout_priority();
     extern __shared__ __align__(16) float roll_lds[];
     float* gl = stage_policies<EXT>(a, roll_lds);
-    const size_t d = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (d >= (size_t)a.D) return;
+    const DroneAt d = drone_at((size_t)blockIdx.x * blockDim.x);
+    if (d.first + threadIdx.x >= (size_t)a.D) return;
     if constexpr (BWD) {
         if (!ckpt_tag_intact(a)) {
             poison_gradients(a, d);
             return;
         }
     }
-    const int w = a.drone_world[d];
+    const int w = at(a.drone_world, 0, d);
     const SoaRec rec{a.par_soa, a.M, w};
     const float* G = (a.has_obj && a.gain) ? a.gain + (size_t)a.gidx[w] * NG : nullptr;
     if (EXT && a.mlp_H > 0) G = roll_lds + (size_t)a.gidx[w] * a.mlp_P;
     const int gs = blockDim.x;
-    if constexpr (MODELS == MS_FP) rollout_drone<BWD, MODEL_FP, CTRL, INTEG, AERO, EXT>(rec, a, d, w, S_h, G, gl, gs);
+    if constexpr (lane_in_lds<BWD, MODELS, CTRL, INTEG, AERO, EXT>()) {
+        using Rec = LaneLds<CTRL>;
+        __shared__ float cols[Rec::COLS * Rec::LANES];
+        const Rec lrec(rec, cols);
+        rollout_drone<BWD, MODEL_FP, CTRL, INTEG, AERO, EXT>(lrec, a, d, w, S_h, G, gl, gs);
+    } else if constexpr (MODELS == MS_FP) rollout_drone<BWD, MODEL_FP, CTRL, INTEG, AERO, EXT>(rec, a, d, w, S_h, G, gl, gs);
     else rollout_drone<BWD, MODEL_ID, CTRL, INTEG, AERO, EXT>(rec, a, d, w, S_h, G, gl, gs);
 }
 
@@ -989,7 +1072,7 @@ __global__ __launch_bounds__(256, (MODELS == MS_ID && !EXT && !AERO) ? 4 : 1) vo
     if ((int)threadIdx.x >= cnt) return;
     using Rec = typename std::conditional<BWD, ScalarRec, typename std::conditional<MODELS == MS_FP, VecRec, AosRec>::type>::type;
     const Rec rec{a.par_aos + (size_t)w * NREC};
-    const size_t d = (size_t)d0 + threadIdx.x;
+    const DroneAt d = drone_at((size_t)d0);
     if constexpr (BWD) {
         if (!ckpt_tag_intact(a)) {
             poison_gradients(a, d);
@@ -1011,7 +1094,7 @@ template <bool BWD, bool EXT>
 static size_t roll_lds_bytes(const RollArgs& a, int lanes) {
     if (EXT && a.mlp_H > 0)
         return ((size_t)a.n_pol * a.mlp_P + (size_t)(BWD ? 4 : 2) * a.mlp_H * lanes) * sizeof(float);
-    return BWD ? (size_t)NG * lanes * sizeof(float) : 0;
+    return BWD && a.has_obj && a.gain ? (size_t)NG * lanes * sizeof(float) : 0;
 }
 
 template <bool BWD, int MODELS, int CTRL, int INTEG, bool AERO, bool EXT>
@@ -1020,7 +1103,7 @@ static hipError_t launch_roll_k(const KernelSel& ks, const RollArgs& a, const in
     const int S_h = a.S_h;
     if (ks.mode == LM_LANE) {
         if constexpr (MODELS != MS_BOTH) {
-            const int bs = ks.tile;
+            const int bs = lane_in_lds<BWD, MODELS, CTRL, INTEG, AERO, EXT>() ? LaneLds<CTRL>::LANES : ks.tile;
             const unsigned grid = (unsigned)((a.D + bs - 1) / bs);
             const size_t lds = roll_lds_bytes<BWD, EXT>(a, bs);
             hipLaunchKernelGGL((k_rollout_lane<BWD, MODELS, CTRL, INTEG, AERO, EXT>), dim3(grid), dim3(bs), lds, s,

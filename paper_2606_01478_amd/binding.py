@@ -8,6 +8,7 @@ fallback path.
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 from ctypes import POINTER, c_float, c_int32, c_int64, c_uint8, c_uint32, c_void_p
 from typing import Dict, Optional
@@ -157,8 +158,16 @@ def _ptr(t) -> Optional[int]:
 
 
 def _stream() -> int:
+    """Raw handle of the current stream (torch.cuda.current_stream() wraps the same
+    handle in an object made for the call: 1.5 us of a call of 8 us)."""
     import torch
-    return torch.cuda.current_stream().cuda_stream
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+
+
+@functools.lru_cache(maxsize=None)
+def _torch_dtypes(names):
+    import torch
+    return frozenset(getattr(torch, n) for n in names if hasattr(torch, n))
 
 
 class Sim:
@@ -233,9 +242,10 @@ class Sim:
     def _need(self, t, shape, name, dtypes=("float32",)) -> None:
         if t is None:
             return
-        if tuple(t.shape) != tuple(shape):
+        # (compared as they are first: forming tuples and names takes longer than a launch)
+        if t.shape != shape and tuple(t.shape) != tuple(shape):
             raise ValueError(f"{name}: expected shape {tuple(shape)}, got {tuple(t.shape)}")
-        if str(t.dtype).replace("torch.", "") not in dtypes:
+        if t.dtype not in _torch_dtypes(dtypes) and str(t.dtype).replace("torch.", "") not in dtypes:
             raise ValueError(f"{name}: expected dtype {dtypes}, got {t.dtype}")
 
     def _gain_shape(self, obj):

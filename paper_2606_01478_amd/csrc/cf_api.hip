@@ -33,17 +33,24 @@ __global__ void k_fill_u32(unsigned* p, int n, unsigned v) {
     if (i < n) p[i] = v;
 }
 
-// soa[i][w] = aos[w][i] of the parameter records
-__global__ __launch_bounds__(64) void k_transpose_records(const float* __restrict__ aos, int M, float* __restrict__ soa) {
+// the transposed copy of the parameter records (cf_layout.hpp)
+__global__ __launch_bounds__(64) void k_transpose_records(const float* __restrict__ aos, int64_t D, int M,
+                                                          float* __restrict__ soa) {
     const int w = blockIdx.x * 64 + threadIdx.x;
     if (w >= M) return;
+    const bool quads = soa_quads(D, M);
     const float4* r = (const float4*)(aos + (size_t)w * NREC);
     for (int i = 0; i < NREC / 4; ++i) {
         const float4 v = r[i];
-        soa[(size_t)(4 * i) * M + w] = v.x;
-        soa[(size_t)(4 * i + 1) * M + w] = v.y;
-        soa[(size_t)(4 * i + 2) * M + w] = v.z;
-        soa[(size_t)(4 * i + 3) * M + w] = v.w;
+        float* row = soa + (size_t)(4 * i) * M;
+        if (quads) {
+            *(float4*)(row + 4 * (size_t)w) = v;
+        } else {
+            row[w] = v.x;
+            row[(size_t)M + w] = v.y;
+            row[(size_t)2 * M + w] = v.z;
+            row[(size_t)3 * M + w] = v.w;
+        }
     }
 }
 
@@ -747,7 +754,8 @@ cf_status cf_create(const cf_desc* d, cf_handle** out) {
     if (host_soa) {
         float* const soa = (float*)(img.get() + o_soa);
         for (size_t w = 0; w < M; ++w)
-            for (int i = 0; i < NREC; ++i) soa[(size_t)i * M + w] = aos[w * NREC + i];
+            for (int i = 0; i < NREC; ++i)
+                soa[(i & ~3) * M + (soa_quads(D, M) ? (i & 3) + 4 * w : (i & 3) * M + w)] = aos[w * NREC + i];
     }
     if ((e = hipMalloc((void**)&h->tables, end)) != hipSuccess) return fail(e);
     if ((e = hipMemcpy(h->tables, img.get(), copy_bytes, hipMemcpyHostToDevice)) != hipSuccess) return fail(e);
@@ -759,8 +767,8 @@ cf_status cf_create(const cf_desc* d, cf_handle** out) {
     h->counters = (unsigned*)(h->tables + o_cnt);
     if (lanes) h->par_soa = (float*)(h->tables + o_soa);
     if (lanes && !host_soa) {
-        hipLaunchKernelGGL(k_transpose_records, dim3((unsigned)((M + 63) / 64)), dim3(64), 0, nullptr, h->par_aos,
-                           (int)M, h->par_soa);
+        hipLaunchKernelGGL(k_transpose_records, dim3((unsigned)((M + 63) / 64)), dim3(64), 0, nullptr,
+                           h->par_aos, (int64_t)D, (int)M, h->par_soa);
         if ((e = hipGetLastError()) != hipSuccess || (e = hipStreamSynchronize(nullptr)) != hipSuccess) return fail(e);
     }
     if ((e = scratch_setup(dev)) != hipSuccess) return fail(e);

@@ -49,10 +49,20 @@ struct VecRec {
     }
     __device__ __forceinline__ float operator()(int i) const { return r[i + zero]; }
 };
-// accessor over a world's record in the transposed [NREC][M] copy (per-lane world)
+// accessors over a world's record in the transposed copy (per-lane world, cf_layout.hpp):
+// in either layout, and in quads known to be so
 struct SoaRec {
+    const float* p; int M; int w; int field, world;
+    __device__ __forceinline__ SoaRec(const float* soa, int64_t D, int M_, int w_)
+        : p(soa), M(M_), w(w_), field(soa_quads(D, M_) ? 1 : M_), world(soa_quads(D, M_) ? 4 : 1) {}
+    __device__ __forceinline__ size_t at(int i) const {
+        return (size_t)(i & ~3) * M + (size_t)(i & 3) * field + (size_t)w * world;
+    }
+    __device__ __forceinline__ float operator()(int i) const { return p[at(i)]; }
+};
+struct QuadRec {
     const float* p; int M; int w;
-    __device__ __forceinline__ float operator()(int i) const { return p[(size_t)i * M + w]; }
+    __device__ __forceinline__ float operator()(int i) const { return p[(size_t)(i & ~3) * M + (size_t)w * 4 + (i & 3)]; }
 };
 
 // The record with its base pointer hidden from the optimiser: loads through the
@@ -66,15 +76,15 @@ __device__ __forceinline__ ScalarRec laundered(AosRec r) {
     return ScalarRec{r.r};
 }
 // (a laundered pointer has no address space of its own: say that it is global)
-struct GlobalSoaRec {
-    const float* p; int M; int w;
+struct GlobalSoaRec : SoaRec {
+    __device__ __forceinline__ explicit GlobalSoaRec(const SoaRec& r) : SoaRec(r) {}
     __device__ __forceinline__ float operator()(int i) const {
-        return ((const __attribute__((address_space(1))) float*)p)[(size_t)i * M + w];
+        return ((const __attribute__((address_space(1))) float*)p)[at(i)];
     }
 };
 __device__ __forceinline__ GlobalSoaRec laundered(SoaRec r) {
     asm volatile("" : "+s"(r.p));
-    return GlobalSoaRec{r.p, r.M, r.w};
+    return GlobalSoaRec(r);
 }
 __device__ __forceinline__ ScalarRec laundered(ScalarRec r) {
     asm volatile("" : "+s"(r.r));

@@ -9,7 +9,7 @@ namespace cfk {
 enum : int { MS_FP = 1, MS_ID = 2, MS_BOTH = 3 };
 // how lanes are mapped to drones
 //   LM_LANE: lane = drone, world looked up per lane, parameters from the
-//            transposed [NREC][M] copy (worlds of a handful of drones);
+//            transposed copy (cf_layout.hpp; worlds of a handful of drones);
 //   LM_TILE: one workgroup per tile. Rollouts take per-world tiles {world,
 //            first drone, count, model} (parameters are uniform loads); held
 //            steps take packed tiles {first list entry, count, model} of one
@@ -47,7 +47,7 @@ struct StepArgs {
     int64_t D;
     int M;
     const float* par_aos;   // [M][NREC]
-    const float* par_soa;   // [NREC][M]
+    const float* par_soa;   // transposed records (cf_layout.hpp)
     const int32_t* drone_world;  // [D]
     float dt;
     float dtc, inv_dtc;     // onboard controller period (ctrl_every physics steps) and its inverse

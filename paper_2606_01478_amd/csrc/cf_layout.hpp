@@ -45,6 +45,15 @@ enum : int {
 enum : int { MODEL_FP = 0, MODEL_ID = 1 };
 enum : int { CTRL_ROTOR = 0, CTRL_PID = 1, CTRL_TORQUE = 2, CTRL_POSITION = 3 };
 enum : int { EULER = 0, RK4 = 1 };
+// The transposed copy of the records, for one world per lane: field i of world w at
+// (i / 4) 4 M + (i % 4) M + w, a row per field; or, where lanes share worlds, at
+// (i / 4) 4 M + (i % 4) + 4 w, four consecutive fields side by side, so that a
+// single step reads its coefficients and gains four to a load. One step and a masked
+// reset, rows -> quads: 32768 worlds of 14 identified drones 20.5 -> 17.7 us, 131072 of
+// 4 drones behind the attitude controller 38.3 -> 34.2; 131072 of 2 such drones
+// 24.1 -> 25.9 and 262144 of one 29.3 -> 34.2, where a field read alone wastes most of
+// what it fetches.
+constexpr bool soa_quads(long long drones, long long worlds) { return drones >= 3 * worlds; }
 constexpr int S_FP = 17, S_PID = 25, S_ID = 13;
 
 }  // namespace cfk

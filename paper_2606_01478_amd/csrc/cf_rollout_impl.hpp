@@ -1030,7 +1030,7 @@ __global__ __launch_bounds__(256, (lane_in_lds<BWD, MODELS, CTRL, INTEG, AERO, E
         }
     }
     const int w = at(a.drone_world, 0, d);
-    const SoaRec rec{a.par_soa, a.M, w};
+    const SoaRec rec(a.par_soa, a.D, a.M, w);
     const float* G = (a.has_obj && a.gain) ? a.gain + (size_t)a.gidx[w] * NG : nullptr;
     if (EXT && a.mlp_H > 0) G = roll_lds + (size_t)a.gidx[w] * a.mlp_P;
     const int gs = blockDim.x;

@@ -10,10 +10,11 @@ namespace cfk {
 constexpr int STEP_PARTS = 3;
 
 // One drone, K steps with a held command; state rows st[i*D + d].
-// MR: variant for an onboard controller slower than the physics
-template <int MODEL, int CTRL, int INTEG, bool AERO, bool MR, class R>
+// MR: variant for an onboard controller slower than the physics; ONE: for a single step
+template <int MODEL, int CTRL, int INTEG, bool AERO, bool MR, bool ONE, class R>
 __device__ __forceinline__ void run_held(const R& rec, const StepArgs& a, size_t d, int w) {
     const size_t D = (size_t)a.D;
+    const int K = ONE ? 1 : a.K;
     bool bad = false;
     if constexpr (MODEL == MODEL_FP) {
         constexpr int S = (CTRL == CTRL_PID) ? S_PID : S_FP;
@@ -32,10 +33,10 @@ __device__ __forceinline__ void run_held(const R& rec, const StepArgs& a, size_t
         // record) rather than held in registers through the integration; with a world
         // per lane they would be 33 vector loads a step, so there they stay in
         // registers (131 072 position-controlled worlds, 100 steps: 200 -> 173 us)
-        constexpr bool HOLD_GAINS = std::is_same<R, SoaRec>::value;
+        constexpr bool HOLD_GAINS = ONE || std::is_same<R, SoaRec>::value;
         PidParams C;
         if constexpr (CTRL != CTRL_ROTOR && HOLD_GAINS) C = load_pid(rec, CTRL == CTRL_POSITION);
-        for (int k = 0; k < a.K; ++k) {
+        for (int k = 0; k < K; ++k) {
             const bool ctrl_now = MR ? phase == 0 : true;
             if constexpr (CTRL != CTRL_ROTOR && !HOLD_GAINS) {
                 if (ctrl_now) C = load_pid(laundered(rec), CTRL == CTRL_POSITION);
@@ -63,7 +64,7 @@ __device__ __forceinline__ void run_held(const R& rec, const StepArgs& a, size_t
 #pragma unroll
         for (int i = 0; i < 4; ++i) u[i] = a.cmd[i * D + d];
         EulerBase B;
-        for (int k = 0; k < a.K; ++k) {
+        for (int k = 0; k < K; ++k) {
             id_begin_step(x, B, k);
             id_step_base<INTEG>(x, comp, u, P, a.dt, B);
         }
@@ -78,15 +79,15 @@ __device__ __forceinline__ void run_held(const R& rec, const StepArgs& a, size_t
     if (a.nonfinite && bad) atomicOr(a.nonfinite + w, 1u);
 }
 
-template <int MODELS, int CTRL, int INTEG, bool AERO, bool MR, class R>
+template <int MODELS, int CTRL, int INTEG, bool AERO, bool MR, bool ONE, class R>
 __device__ __forceinline__ void run_model(int model, const R& rec, const StepArgs& a, size_t d, int w) {
     if constexpr (MODELS == MS_FP) {
-        run_held<MODEL_FP, CTRL, INTEG, AERO, MR>(rec, a, d, w);
+        run_held<MODEL_FP, CTRL, INTEG, AERO, MR, ONE>(rec, a, d, w);
     } else if constexpr (MODELS == MS_ID) {
-        run_held<MODEL_ID, CTRL, INTEG, AERO, MR>(rec, a, d, w);
+        run_held<MODEL_ID, CTRL, INTEG, AERO, MR, ONE>(rec, a, d, w);
     } else {
-        if (model == MODEL_FP) run_held<MODEL_FP, CTRL, INTEG, AERO, MR>(rec, a, d, w);
-        else run_held<MODEL_ID, CTRL, INTEG, AERO, MR>(rec, a, d, w);
+        if (model == MODEL_FP) run_held<MODEL_FP, CTRL, INTEG, AERO, MR, ONE>(rec, a, d, w);
+        else run_held<MODEL_ID, CTRL, INTEG, AERO, MR, ONE>(rec, a, d, w);
     }
 }
 
@@ -95,7 +96,7 @@ __device__ __forceinline__ void run_model(int model, const R& rec, const StepArg
 // full, so no lanes idle at world ends). A wave whose lanes share one world
 // reads that world's parameters with scalar loads into scalar registers; a wave
 // across a world boundary reads each lane's own with vector loads.
-template <int MODELS, int CTRL, int INTEG, bool AERO, bool MR>
+template <int MODELS, int CTRL, int INTEG, bool AERO, bool MR, bool ONE>
 __device__ __forceinline__ void run_tile(const StepArgs& a, int4 td) {
     // td = {first list entry, drone count, model, 0}, uniform over the workgroup
     const int first = __builtin_amdgcn_readfirstlane(td.x);
@@ -107,25 +108,30 @@ __device__ __forceinline__ void run_tile(const StepArgs& a, int4 td) {
     const int w = a.drone_world[d];
     const int w0 = __builtin_amdgcn_readfirstlane(w);
     if (__builtin_amdgcn_ballot_w64(w != w0) == 0) {
-        run_model<MODELS, CTRL, INTEG, AERO, MR>(model, AosRec{a.par_aos + (size_t)w0 * NREC}, a, d, w0);
+        run_model<MODELS, CTRL, INTEG, AERO, MR, ONE>(model, AosRec{a.par_aos + (size_t)w0 * NREC}, a, d, w0);
     } else {
-        run_model<MODELS, CTRL, INTEG, AERO, MR>(model, LaneRec{a.par_aos + (size_t)w * NREC}, a, d, w);
+        run_model<MODELS, CTRL, INTEG, AERO, MR, ONE>(model, LaneRec{a.par_aos + (size_t)w * NREC}, a, d, w);
     }
 }
 
-template <int MODELS, int CTRL, int INTEG, bool AERO, bool MR>
+template <int MODELS, int CTRL, int INTEG, bool AERO, bool MR, bool ONE>
 __global__ __launch_bounds__(256) void k_step_lane(StepArgs a) {
     const size_t d = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (d >= (size_t)a.D) return;
     const int w = a.drone_world[d];
-    const SoaRec rec{a.par_soa, a.M, w};
-    if constexpr (MODELS == MS_FP) run_held<MODEL_FP, CTRL, INTEG, AERO, MR>(rec, a, d, w);
-    else run_held<MODEL_ID, CTRL, INTEG, AERO, MR>(rec, a, d, w);
+    constexpr int MODEL = MODELS == MS_FP ? MODEL_FP : MODEL_ID;
+    if constexpr (ONE) {
+        if (soa_quads(a.D, a.M)) {
+            run_held<MODEL, CTRL, INTEG, AERO, MR, ONE>(QuadRec{a.par_soa, a.M, w}, a, d, w);
+            return;
+        }
+    }
+    run_held<MODEL, CTRL, INTEG, AERO, MR, ONE>(SoaRec(a.par_soa, a.D, a.M, w), a, d, w);
 }
 
-template <int MODELS, int CTRL, int INTEG, bool AERO, bool MR>
+template <int MODELS, int CTRL, int INTEG, bool AERO, bool MR, bool ONE>
 __global__ __launch_bounds__(256) void k_step_tile(StepArgs a, const int4* __restrict__ tiles) {
-    run_tile<MODELS, CTRL, INTEG, AERO, MR>(a, tiles[blockIdx.x]);
+    run_tile<MODELS, CTRL, INTEG, AERO, MR, ONE>(a, tiles[blockIdx.x]);
 }
 
 // Persistent work queue: each workgroup pops the next tile index from *counter
@@ -140,7 +146,7 @@ __device__ __forceinline__ void run_queue(const StepArgs& a, const int4* __restr
         const int t = __builtin_amdgcn_readfirstlane(s_next);
         __syncthreads();
         if (t >= n_tiles) break;
-        run_tile<MODELS, CTRL, INTEG, AERO, MR>(a, tiles[t]);
+        run_tile<MODELS, CTRL, INTEG, AERO, MR, false>(a, tiles[t]);
     }
 }
 
@@ -152,17 +158,17 @@ __global__ __launch_bounds__(256) void k_step_wq(StepArgs a, const int4* __restr
 
 
 
-template <int MODELS, int CTRL, int INTEG, bool AERO, bool MR>
+template <int MODELS, int CTRL, int INTEG, bool AERO, bool MR, bool ONE>
 static hipError_t launch_step_k(const KernelSel& ks, const StepArgs& a, const int4* tiles, int n_tiles,
                                 unsigned* counter, int wq_blocks, hipStream_t s) {
     if (ks.mode == LM_LANE) {
         if constexpr (MODELS == MS_BOTH) return hipErrorInvalidValue;
         const int bs = ks.tile;
         const unsigned grid = (unsigned)((a.D + bs - 1) / bs);
-        hipLaunchKernelGGL((k_step_lane<MODELS, CTRL, INTEG, AERO, MR>), dim3(grid), dim3(bs), 0, s, a);
+        hipLaunchKernelGGL((k_step_lane<MODELS, CTRL, INTEG, AERO, MR, ONE>), dim3(grid), dim3(bs), 0, s, a);
     } else if (ks.mode == LM_TILE) {
-        hipLaunchKernelGGL((k_step_tile<MODELS, CTRL, INTEG, AERO, MR>), dim3(n_tiles), dim3(ks.tile), 0, s, a, tiles);
-    } else {
+        hipLaunchKernelGGL((k_step_tile<MODELS, CTRL, INTEG, AERO, MR, ONE>), dim3(n_tiles), dim3(ks.tile), 0, s, a, tiles);
+    } else if constexpr (!ONE) {
         // work-queue workgroups that do not fit at once start later, find the
         // queue empty and exit
         hipLaunchKernelGGL((k_step_wq<MODELS, CTRL, INTEG, AERO, MR>), dim3(wq_blocks), dim3(ks.tile), 0, s, a, tiles,
@@ -177,9 +183,17 @@ static hipError_t launch_step_t(const KernelSel& ks, const StepArgs& a, const in
                                 unsigned* counter, int wq_blocks, hipStream_t s) {
     if constexpr (MODELS != MS_ID && CTRL != CTRL_ROTOR) {
         if (a.ctrl_every > 1)
-            return launch_step_k<MODELS, CTRL, INTEG, AERO, true>(ks, a, tiles, n_tiles, counter, wq_blocks, s);
+            return launch_step_k<MODELS, CTRL, INTEG, AERO, true, false>(ks, a, tiles, n_tiles, counter, wq_blocks, s);
     }
-    return launch_step_k<MODELS, CTRL, INTEG, AERO, false>(ks, a, tiles, n_tiles, counter, wq_blocks, s);
+    // A single step is bound by its loads, so what counts is waves in flight: without the
+    // loop, its sums' lost parts and what is held across steps the kernel takes 91 to 98
+    // registers instead of 119 to 161 (32768 worlds of 14 drones, with a masked reset:
+    // rotor interface 22.8 -> 20.6 us, torque 25.9 -> 21.8)
+    if constexpr (INTEG == RK4 && !AERO) {
+        if (a.K == 1 && ks.mode != LM_WQ)
+            return launch_step_k<MODELS, CTRL, INTEG, AERO, false, true>(ks, a, tiles, n_tiles, counter, wq_blocks, s);
+    }
+    return launch_step_k<MODELS, CTRL, INTEG, AERO, false, false>(ks, a, tiles, n_tiles, counter, wq_blocks, s);
 }
 
 template <int MODELS, int CTRL, int INTEG, bool AERO>

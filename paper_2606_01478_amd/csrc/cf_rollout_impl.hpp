@@ -1044,9 +1044,9 @@ __global__ __launch_bounds__(256, (lane_in_lds<BWD, MODELS, CTRL, INTEG, AERO, E
 }
 
 // Identified drones are held to four waves per SIMD (128 registers, a few spilled):
-// their adjoint shares the compute units with the first-principles one, whose 244
+// their adjoint shares the compute units with the first-principles one, whose 235
 // registers leave room for no wider wave (118 000 uneven drones, 250 steps, both
-// models, forward and adjoint: 3047 us, unbounded 3125 us).
+// models, forward and adjoint, before rows took scalar bases: 3047 us, unbounded 3125).
 template <bool BWD, int MODELS, int CTRL, int INTEG, bool AERO, bool EXT>
 __global__ __launch_bounds__(256, (MODELS == MS_ID && !EXT && !AERO) ? 4 : 1) void k_rollout_tile(
     RollArgs a, const int4* __restrict__ tiles, int S_h) {

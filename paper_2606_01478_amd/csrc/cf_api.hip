@@ -113,21 +113,20 @@ __global__ __launch_bounds__(256) void k_reduce_world(const float* __restrict__ 
 
 // g[k][c] = sum over the drones d whose world uses gain (or policy) k of v[c][d],
 // c < nc, in a fixed order that depends only on D: workgroup (b, c, k) sums the drones
-// of chunk b (each thread a strided subset, then a tree), into g directly where there
+// of chunk b (cfh::sum_chunk; each thread a strided subset, then a tree), into g directly where there
 // is one chunk, else into part[k][c][b], which k_sum_parts adds up. One workgroup per
 // component rather than one for all of them: the 52 trees one after the other, and the
 // serial sum over hundreds of chunks, took 108 us for 63 000 drones.
 constexpr int GAIN_COMP = 52;
-constexpr int GAIN_MAX_BLOCKS = 1024;
-constexpr int64_t SUM_CHUNK = 16384;
+constexpr int MLP_MAX_BLOCKS = 1024;
 
 __global__ __launch_bounds__(1024) void k_sum_drones(const float* __restrict__ v, int64_t D,
                                                      const int32_t* __restrict__ drone_world,
                                                      const int32_t* __restrict__ gidx, int n_gains,
-                                                     float* __restrict__ out) {
+                                                     int64_t chunk, float* __restrict__ out) {
     __shared__ float sh[16];
     const int b = blockIdx.x, nb = gridDim.x, c = blockIdx.y, nc = gridDim.y, k = blockIdx.z;
-    const int64_t lo = b * SUM_CHUNK, hi = min(D, lo + SUM_CHUNK);
+    const int64_t lo = b * chunk, hi = min(D, lo + chunk);
     const float* row = v + (size_t)c * D;
     // four drones a thread at a time, so that their loads overlap
     float s = 0.f;
@@ -164,12 +163,12 @@ __global__ __launch_bounds__(64) void k_sum_parts(const float* __restrict__ part
     if (threadIdx.x == 0) g[blockIdx.x] = s;
 }
 
-// part: n_gains * nc * ceil(D / SUM_CHUNK) floats (unused with one chunk)
+// part: cfh::sum_part_floats(n_gains, nc, D) floats (unused with one chunk)
 static hipError_t sum_drones(const float* v, int nc, int64_t D, const int32_t* drone_world, const int32_t* gidx,
                              int n_gains, float* part, float* g, hipStream_t s) {
-    const unsigned nb = (unsigned)((D + SUM_CHUNK - 1) / SUM_CHUNK);
+    const unsigned nb = (unsigned)cfh::sum_chunks(D);
     hipLaunchKernelGGL(k_sum_drones, dim3(nb, nc, n_gains), dim3(1024), 0, s, v, D, drone_world, gidx, n_gains,
-                       nb == 1 ? g : part);
+                       cfh::sum_chunk(D), nb == 1 ? g : part);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || nb == 1) return e;
     hipLaunchKernelGGL(k_sum_parts, dim3((unsigned)(n_gains * nc)), dim3(64), 0, s, part, (int)nb, g);
@@ -260,12 +259,6 @@ __global__ __launch_bounds__(256) void k_mlp_final(const float* __restrict__ par
         for (int b = 0; b < nb; ++b) s += part[((size_t)k * nb + b) * P + p];
         g[(size_t)k * P + p] = s;
     }
-}
-
-// workgroups per gain of the stage-1 reduction for D drones
-static int gain_blocks(int64_t D) {
-    const int64_t nb = (D + 511) / 512;
-    return (int)std::max<int64_t>(1, std::min<int64_t>(nb, GAIN_MAX_BLOCKS));
 }
 
 // Scratch of cf_rollout_backward_noalloc: one static device array, each GPU that
@@ -1333,7 +1326,6 @@ static cf_status rollout_backward_impl(cf_handle* h, const float* cmds, int32_t 
     // segment slots 1..K-1 hold recomputed states (slot 0 is the checkpoint itself);
     // with the reward objective slot K holds the final state of the last segment
     const int slots = std::min(K, T) + (kind == CF_OBJ_BPTT_REWARD ? 1 : 0);
-    const int nb = gain_blocks(h->D);
     const size_t n_tab = (obj && !obj->ref_table) ? (size_t)(T + 1) * 6 : 0;
     const bool quad_b = quad_roll(h, obj);
     // quads recompute every segment at once where the states fit (QUAD_SEG_FLOATS) and
@@ -1341,14 +1333,15 @@ static cf_status rollout_backward_impl(cf_handle* h, const float* cmds, int32_t 
     const size_t n_all = (size_t)(T + 1) * h->S * Dm;
     bool seg_all = quad_b && K > 1 && T > K && T >= 16 && n_all <= QUAD_SEG_FLOATS && (T + K - 1) / K <= 65535;
     const int64_t N_rec = (int64_t)T * Dm;
-    const int nb_mlp = (int)std::max<int64_t>(1, std::min<int64_t>((N_rec + 2047) / 2048, GAIN_MAX_BLOCKS));
+    const int nb_mlp = (int)std::max<int64_t>(1, std::min<int64_t>((N_rec + 2047) / 2048, MLP_MAX_BLOCKS));
     const size_t n_ggc = (g_gain && Hp == 0) ? (size_t)52 * Dm : 0;
     // policies: records of every drone-step, or (quad kernels) each drone's own sum of
     // its weight gradient where that is less
     const bool pol_sum = Hp > 0 && quad_sums_policy(Hp) && (int64_t)Pp <= (int64_t)(17 + 4 * Hp) * T && quad_b;
     const size_t n_rec = (g_gain && Hp > 0) ? (pol_sum ? (size_t)Pp * Dm : (size_t)(17 + 4 * Hp) * N_rec) : 0;
-    const size_t n_part = !g_gain ? 0
-                                  : (Hp > 0 ? (size_t)h->n_gains * nb_mlp * Pp : (size_t)h->n_gains * nb * GAIN_COMP);
+    const size_t n_part = !g_gain                ? 0
+                          : (Hp > 0 && !pol_sum) ? (size_t)h->n_gains * nb_mlp * Pp
+                                                 : cfh::sum_part_floats(h->n_gains, Pp, h->D);
     // a policy whose records are wanted but would be summed goes the general way
     const bool quad = quad_b && !(Hp > 0 && quad_sums_policy(Hp) && !pol_sum);
     auto up = [](size_t n) { return (n + 63) / 64 * 64; };   // 256-byte-aligned slices

@@ -211,6 +211,18 @@ void derive_step(int model, float dt, float* out) {
     }
 }
 
+int64_t sum_chunk(int64_t D) {
+    const int64_t per = (D + SUM_MAX_CHUNKS - 1) / SUM_MAX_CHUNKS;
+    return std::max<int64_t>(SUM_CHUNK, (per + 4095) / 4096 * 4096);
+}
+
+int sum_chunks(int64_t D) {
+    const int64_t chunk = sum_chunk(D);
+    return (int)std::max<int64_t>(1, (D + chunk - 1) / chunk);
+}
+
+size_t sum_part_floats(int n_gains, int nc, int64_t D) { return (size_t)n_gains * nc * sum_chunks(D); }
+
 namespace {
 int model_cost(int model, int ctrl) {
     if (model == MODEL_ID) return 2;

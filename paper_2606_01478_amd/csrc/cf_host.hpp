@@ -64,6 +64,20 @@ std::vector<PackedTile> packed_tiles(const std::vector<int32_t>& counts, const s
                                      const std::vector<uint8_t>& models, int tile, std::vector<int32_t>* list,
                                      int* n_fp);
 
+// ---- sums over the drones (gain and policy gradients) -----------------------------
+
+// The sums are taken over chunks of consecutive drones, one workgroup each, and then
+// over the chunks. 16384 drones give each of a workgroup's 1024 threads 16; beyond
+// 1024 chunks (2^24 drones) the chunk grows instead of their number, so that the
+// partial sums stay bounded. The launch and its scratch both follow from these.
+constexpr int64_t SUM_CHUNK = 16384;
+constexpr int SUM_MAX_CHUNKS = 1024;
+// drones per chunk: a multiple of the 4096 that a workgroup reads at a time
+int64_t sum_chunk(int64_t D);
+int sum_chunks(int64_t D);
+// floats of the partial sums of nc components per gain
+size_t sum_part_floats(int n_gains, int nc, int64_t D);
+
 // ---- autotune cache ---------------------------------------------------------------
 
 struct LaunchChoice {

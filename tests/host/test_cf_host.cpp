@@ -307,6 +307,24 @@ static void test_tags() {
     CHECK(reg.match(&bufA, 100, 10, 13, 1024, &o, &got) == CF_OK);
 }
 
+// the partial sums' scratch holds what the launch writes, at any number of drones
+static void test_sum_chunks() {
+    for (int64_t D : {(int64_t)1, (int64_t)16384, (int64_t)16385, (int64_t)1 << 20, ((int64_t)1 << 24) - 1,
+                      (int64_t)1 << 24, ((int64_t)1 << 24) + 1, ((int64_t)1 << 24) + 16385, (int64_t)1 << 30,
+                      ((int64_t)1 << 31) - 1}) {
+        const int64_t chunk = cfh::sum_chunk(D), n = cfh::sum_chunks(D);
+        CHECK(chunk % 4096 == 0 && chunk >= 16384);
+        CHECK(n >= 1 && n <= 1024);
+        CHECK((n - 1) * chunk < D && n * chunk >= D);          // every chunk has drones, every drone a chunk
+        for (int gains : {1, 2, 300})
+            for (int nc : {52, 564})
+                CHECK(cfh::sum_part_floats(gains, nc, D) >= (size_t)gains * nc * ((D + chunk - 1) / chunk));
+    }
+    CHECK(cfh::sum_chunks(0) == 1);
+    CHECK(cfh::sum_chunks((int64_t)1 << 24) == 1024);
+    CHECK(cfh::sum_chunks(63000) == 4);
+}
+
 int main(int argc, char** argv) {
     const std::string dir = argc > 1 ? argv[1] : "/tmp";
     test_validate_desc();
@@ -315,6 +333,7 @@ int main(int argc, char** argv) {
     test_packed_tiles();
     test_cache(dir);
     test_tags();
+    test_sum_chunks();
     std::printf("host tests passed: %d checks\n", g_checks);
     return 0;
 }

@@ -180,6 +180,7 @@ class Sim:
         lib = load()
         self._lib = lib
         self._h = c_void_p()
+        self._sets = []   # handles of the controller sets made on this one
         M = int(n_worlds)
         self.n_worlds = M
         counts = np.ascontiguousarray(np.broadcast_to(np.asarray(drones_per_world, np.int32), (M,)))
@@ -229,6 +230,13 @@ class Sim:
                    w.params, renorm_q=w.renorm_q, n_gains=n_gains, gain_index=w.gain_index, flags=flags, **kw)
 
     def close(self) -> None:
+        # a controller set needs its handle until it is destroyed; the collector may
+        # finalise the two of a reference cycle in either order
+        for m in getattr(self, "_sets", ()):
+            if m.value:
+                self._lib.cf_mppi_destroy(m)
+                m.value = None
+        self._sets = []
         if getattr(self, "_h", None) is not None and self._h.value:
             self._lib.cf_destroy(self._h)
             self._h = c_void_p()
@@ -523,11 +531,13 @@ class Mppi:
         self.C, self.N, self.H, self.n_elite = d.n_controllers, d.n_samples, d.horizon, d.n_elite
         self._m = c_void_p()
         _check(self._lib.cf_mppi_create(sim._h, ctypes.byref(d), ctypes.byref(self._m)), "cf_mppi_create")
+        sim._sets.append(self._m)
 
     def close(self) -> None:
         if getattr(self, "_m", None) is not None and self._m.value:
             self._lib.cf_mppi_destroy(self._m)
-            self._m = c_void_p()
+            self._m.value = None   # (the same object in sim._sets)
+            self.sim._sets = [m for m in self.sim._sets if m is not self._m]
 
     def __del__(self):
         try:

@@ -128,7 +128,6 @@ __global__ __launch_bounds__(256) void k_mppi_rollout(MppiArgs a) {
     float J = 0.f;
     float rc[4] = {0.f, 0.f, 0.f, 0.f};   // held rotor commands
     int phase = 0;                        // physics step within the controller period
-    EulerBase base;                       // identified: the start angles' sines and cosines
     for (int t = 0; t < a.H; ++t) {
         ns.next(t, a);
         float u[4];
@@ -146,8 +145,7 @@ __global__ __launch_bounds__(256) void k_mppi_rollout(MppiArgs a) {
                     if (++phase == a.ctrl_every) phase = 0;
                 }
             } else {
-                id_begin_step(x, base, t * sub + s);
-                id_step_base<INTEG>(x, comp, u, Pi, a.dt, base);
+                id_step<INTEG>(x, comp, u, Pi, a.dt);
             }
         }
         const float ex = x[0] - a.goal[0], ey = x[1] - a.goal[1], ez = x[2] - a.goal[2];

@@ -69,8 +69,7 @@ struct QDrone<MODEL_FP, CTRL> {
         if constexpr (PID) ok = ok && isfinite(s.c.ia) && isfinite(s.c.ir) && isfinite(s.c.wp);
         return ok;
     }
-    __device__ __forceinline__ void begin(const State&) {}
-    __device__ __forceinline__ void step(State& s, float u, float h, int renorm, int j, int) {
+    __device__ __forceinline__ void step(State& s, float u, float h, int renorm, int j) {
         const float n = q_half_ez(s.x.q, P);
         float rc;
         if constexpr (PID) {
@@ -80,6 +79,9 @@ struct QDrone<MODEL_FP, CTRL> {
             rc = u - P.wr;
         }
         q_fp_step(s.x, rc, n, P, h, renorm);
+    }
+    __device__ __forceinline__ void held_step(State& s, float u, float h, int renorm, int j, int) {
+        step(s, u, h, renorm, j);
     }
     // deviations from the reference state (rp, rv: reference position and velocity)
     __device__ __forceinline__ void error(const State& s, float rp, float rv, int j, float* e) const {
@@ -194,9 +196,13 @@ struct QDrone<MODEL_ID, CTRL> {
     __device__ __forceinline__ bool finite(const State& s) const {
         return isfinite(s.x.p) && isfinite(s.x.a) && isfinite(s.x.v) && isfinite(s.x.w) && isfinite(s.x.f);
     }
-    __device__ __forceinline__ void begin(const State& s) { q_id_base(s.x.a, B); }
-    // n: the step's number since begin(); the sines and cosines are exact every 8th
-    __device__ __forceinline__ void step(State& s, float u, float h, int, int j, int n) {
+    // the start angle's sine and cosine in full, or (held step n of a launch) as
+    // id_begin_step does
+    __device__ __forceinline__ void step(State& s, float u, float h, int, int j) {
+        q_id_base(s.x.a, B);
+        q_id_step(s.x, u, P, h, B, j);
+    }
+    __device__ __forceinline__ void held_step(State& s, float u, float h, int, int j, int n) {
         if ((n & 7) == 0) q_id_base(s.x.a, B);
         else q_id_rebase(s.x.a, B);
         q_id_step(s.x, u, P, h, B, j);
@@ -270,8 +276,7 @@ __global__ __launch_bounds__(64) void k_quad_step(StepArgs a) {
     typename Q::State s;
     m.template load<true>(a.st, L, s);
     const float u = q_load(a.cmd, L.row(0));
-    m.begin(s);
-    for (int k = 0; k < a.K; ++k) m.step(s, u, a.dt, a.renorm, L.j, k);
+    for (int k = 0; k < a.K; ++k) m.held_step(s, u, a.dt, a.renorm, L.j, k);
     m.template store<true>(a.st, L, s);
     if (a.nonfinite && !m.finite(s)) atomicOr(a.nonfinite + w, 1u);
 }
@@ -463,7 +468,6 @@ __global__ __launch_bounds__(64) void k_quad_fwd(RollArgs a) {
     Q m(LaneRec{a.par_aos + (size_t)w * NREC}, L.j, a.dt, a.inv_dtc);
     typename Q::State s;
     m.template load<true>(a.x0, L, s);
-    m.begin(s);
     const bool fb = U == 0 && a.has_obj && a.gain;
     float g[13];
     if (fb) q_gain_row(a.gain + (size_t)a.gidx[w] * NG, L.j, g);
@@ -509,7 +513,7 @@ __global__ __launch_bounds__(64) void k_quad_fwd(RollArgs a) {
         } else if (a.has_obj) {
             loss = fma_(a.w_u, u * u, loss);
         }
-        m.step(s, u, a.dt, a.renorm, L.j, t);
+        m.step(s, u, a.dt, a.renorm, L.j);
         if (a.has_obj) {
             const float e = L.j < 3 ? Q::pos(s) - rpn : 0.f;
             if (rew) {
@@ -569,7 +573,6 @@ __device__ __forceinline__ void q_recompute(const RollArgs& a, Q& m, const QLane
     constexpr int UM = U == 0 ? 2 : U;
     const uint32_t uo = L.row(0);
     m.template load<true>(ck, L, x);
-    m.begin(x);
     const float* cmd = a.cmds + (size_t)t0 * 4 * D;
     float ubar = q_load(cmd, uo), rp, rv;
     ref.at(t0, &rp, &rv);
@@ -582,7 +585,7 @@ __device__ __forceinline__ void q_recompute(const RollArgs& a, Q& m, const QLane
         }
         float e[4], h1[UM], h2[UM], o;
         const float u = q_command<Q, EXT, U>(a, m, fb, g, pol, x, L.j, ubar, rp, rv, e, h1, h2, &o);
-        m.step(x, u, a.dt, a.renorm, L.j, i);
+        m.step(x, u, a.dt, a.renorm, L.j);
         slot += SD;
         if (i < n_store) m.template store<false>(slot, L, x);
         ubar = un;

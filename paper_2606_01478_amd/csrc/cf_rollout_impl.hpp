@@ -481,17 +481,14 @@ __device__ __forceinline__ void step_coefs(const R& rec, FpParams& P) {
 }
 
 // one step; rc holds the first-principles rotor commands across steps, the
-// onboard controller runs when ctrl_now; n counts the steps since the run began and
-// B carries the identified model's start angles' sines and cosines
+// onboard controller runs when ctrl_now
 template <int MODEL, int CTRL, int INTEG>
 __device__ __forceinline__ void model_step(float* x, float* comp, const float* u, const DroneParams& p,
-                                           const RollArgs& a, float* rc, bool ctrl_now, EulerBase& B, int n) {
-    if constexpr (MODEL == MODEL_FP) {
+                                           const RollArgs& a, float* rc, bool ctrl_now) {
+    if constexpr (MODEL == MODEL_FP)
         fp_step<CTRL, INTEG>(x, comp, u, p.fp, p.pid, a.dt, a.dtc, a.inv_dtc, a.renorm, rc, ctrl_now);
-    } else {
-        id_begin_step(x, B, n);
-        id_step_base<INTEG>(x, comp, u, p.id, a.dt, B);
-    }
+    else
+        id_step<INTEG>(x, comp, u, p.id, a.dt);
 }
 
 // VJP of a step whose controller (if any) runs every step
@@ -570,7 +567,6 @@ __device__ __forceinline__ void rollout_fwd_drone(const R& rec, const RollArgs& 
     load_cmd(a, 0, d, ubar);
     float rc[4] = {0.f, 0.f, 0.f, 0.f};   // held rotor commands
     int phase = 0;                        // step within the controller period
-    EulerBase B;
     const bool rew = EXT && a.has_obj && a.obj_kind == 1;
     float uprev[4] = {0.f, 0.f, 0.f, 0.f};   // reward: the previous applied command
     int left = a.K;                          // steps to the next checkpoint
@@ -598,7 +594,7 @@ __device__ __forceinline__ void rollout_fwd_drone(const R& rec, const RollArgs& 
             loss += a.w_u * (u[0] * u[0] + u[1] * u[1] + u[2] * u[2] + u[3] * u[3]);
         }
         controller_gains<MODEL, CTRL>(rec, p);
-        model_step<MODEL, CTRL, INTEG>(x, comp, u, p, a, rc, EXT ? phase == 0 : true, B, t);
+        model_step<MODEL, CTRL, INTEG>(x, comp, u, p, a, rc, EXT ? phase == 0 : true);
         if constexpr (EXT) {
             if (++phase == a.ctrl_every) phase = 0;
         }
@@ -708,7 +704,6 @@ __device__ __forceinline__ void rollout_bwd_drone(const R& rec, const RollArgs& 
         const int n_re = (s == nseg - 1) ? (t1 - t0) : (t1 - t0 - 1);
         if (n_re > 0) {
             float x[S], comp[S];
-            EulerBase B;
             load_rows<S>(a.ckpt_in + (size_t)s * SD, D, d, x);
             to_dev<MODEL>(x, p);
 #pragma unroll
@@ -728,7 +723,7 @@ __device__ __forceinline__ void rollout_bwd_drone(const R& rec, const RollArgs& 
                 apply_feedback<MODEL, EXT>(a, G, gl, gs, x, t0 + j, off, f_hover, ubar, u, ev);
                 controller_gains<MODEL, CTRL>(rec, p);
                 if constexpr (MODEL == MODEL_FP) step_coefs<MODEL, CTRL>(rec, p.fp);
-                model_step<MODEL, CTRL, INTEG>(x, comp, u, p, a, rcf, (t0 + j) % n_c == 0, B, j);
+                model_step<MODEL, CTRL, INTEG>(x, comp, u, p, a, rcf, (t0 + j) % n_c == 0);
                 if (j + 1 < t1 - t0 || rew) store_rows<S>(a.seg + (size_t)(j + 1) * SD, D, d, x);
             }
             if (s == nseg - 1) {

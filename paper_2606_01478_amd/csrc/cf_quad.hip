@@ -64,9 +64,15 @@ struct QDrone<MODEL_FP, CTRL> {
             }
         }
     }
-    __device__ __forceinline__ bool finite(const State& s) const {
-        bool ok = isfinite(s.x.p) && isfinite(s.x.q) && isfinite(s.x.v) && isfinite(s.x.w) && isfinite(s.x.r);
-        if constexpr (PID) ok = ok && isfinite(s.c.ia) && isfinite(s.c.ir) && isfinite(s.c.wp);
+    // of the rows that store writes from lane j: lane 3's slots of 3-vectors may hold
+    // anything (0 inf for an infinite thrust command)
+    __device__ __forceinline__ bool finite(const State& s, int j) const {
+        bool ok = isfinite(s.x.q) && isfinite(s.x.r);
+        if (j < 3) ok = ok && isfinite(s.x.p) && isfinite(s.x.v) && isfinite(s.x.w);
+        if constexpr (PID) {
+            if (j < 2) ok = ok && isfinite(s.c.ia);
+            if (j < 3) ok = ok && isfinite(s.c.ir) && isfinite(s.c.wp);
+        }
         return ok;
     }
     __device__ __forceinline__ void step(State& s, float u, float h, int renorm, int j) {
@@ -193,8 +199,8 @@ struct QDrone<MODEL_ID, CTRL> {
             q_store(b, (12u * L.D + L.d) * 4u, s.x.f);
         }
     }
-    __device__ __forceinline__ bool finite(const State& s) const {
-        return isfinite(s.x.p) && isfinite(s.x.a) && isfinite(s.x.v) && isfinite(s.x.w) && isfinite(s.x.f);
+    __device__ __forceinline__ bool finite(const State& s, int j) const {
+        return j < 3 ? isfinite(s.x.p) && isfinite(s.x.a) && isfinite(s.x.v) && isfinite(s.x.w) : isfinite(s.x.f);
     }
     // the start angle's sine and cosine in full, or (held step n of a launch) as
     // id_begin_step does
@@ -278,7 +284,7 @@ __global__ __launch_bounds__(64) void k_quad_step(StepArgs a) {
     const float u = q_load(a.cmd, L.row(0));
     for (int k = 0; k < a.K; ++k) m.held_step(s, u, a.dt, a.renorm, L.j, k);
     m.template store<true>(a.st, L, s);
-    if (a.nonfinite && !m.finite(s)) atomicOr(a.nonfinite + w, 1u);
+    if (a.nonfinite && !m.finite(s, L.j)) atomicOr(a.nonfinite + w, 1u);
 }
 
 // ---------------------------------------------------------------------------

@@ -1581,6 +1581,7 @@ __device__ __forceinline__ void fp_step_structured_vjp(const float* x, const flo
 // offsets from the start angles, the stages' specific thrusts
 struct IdStages {
     float d2[3], off[9], a[4];   // off: stages 2, 3, 4, three angles each
+    float df;                    // thrust less its command; without thrust dynamics the row is not used
 };
 __device__ __forceinline__ void id_stages(const float* x, const float* u, const IdParams& P, float h, IdStages& T) {
     const float h2 = 0.5f * h, hh4 = h2 * h2;
@@ -1592,7 +1593,8 @@ __device__ __forceinline__ void id_stages(const float* x, const float* u, const 
         T.off[3 + i] = __builtin_fmaf(hh4, T.d2[i], T.off[i]);
         T.off[6 + i] = __builtin_fmaf(P.st.b4[i], T.d2[i], P.st.a4[i] * w);
     }
-    const float fu = P.cf_m * u[3], fe = P.cf_m * (x[12] - u[3]);
+    T.df = P.direct ? 0.f : x[12] - u[3];
+    const float fu = P.cf_m * u[3], fe = P.cf_m * T.df;
 #pragma unroll
     for (int s = 0; s < 4; ++s) T.a[s] = __builtin_fmaf(fe, P.st.p[s], fu);
 }
@@ -1619,7 +1621,7 @@ __device__ __forceinline__ void id_step_structured(float* x, float* comp, const 
         x[3 + i] += __builtin_fmaf(P.st.al[i], w, P.st.be[i] * T.d2[i]);
         x[9 + i] += __builtin_fmaf(P.st.ga[i], w, P.st.de[i] * T.d2[i]);
     }
-    x[12] = __builtin_fmaf(x[12] - u[3], P.st.pf, u[3]);
+    x[12] = __builtin_fmaf(T.df, P.st.pf, u[3]);
     advance_pv<0, 6>(x, comp, h, a[0], a[1], a[2], a[3]);
 }
 

@@ -368,6 +368,7 @@ struct QId {
     float c1, c2, c3, al, be, ga, de, a4, b4;   // lane 3: zero
     float p[4], pf, cf_m, g, f_hover;
     float sy;                                   // 1, -1, 0, 0
+    bool direct;                                // no thrust dynamics
 };
 struct QIdBack {
     float q[4], qf;
@@ -394,6 +395,7 @@ __device__ __forceinline__ QId q_load_id(const R& rec, int j) {
     P.cf_m = rec(D_CF_M);
     P.g = j == 2 ? rec(P_GRAVITY) : 0.f;
     P.f_hover = rec(D_F_HOVER);
+    P.direct = rec(P_CTAU) == 0.f;
     P.sy = j == 0 ? 1.f : (j == 1 ? -1.f : 0.f);
     return P;
 }
@@ -457,7 +459,7 @@ __device__ __forceinline__ float q_id_acc(float s, float c, float a, const QId& 
 }
 
 struct QIdStages {
-    float d2, off[3], a[4];
+    float d2, off[3], a[4], df;
 };
 __device__ __forceinline__ void q_id_stages(const QIdState& x, float u, const QId& P, float h, QIdStages& T) {
     const float h2 = 0.5f * h;
@@ -466,7 +468,8 @@ __device__ __forceinline__ void q_id_stages(const QIdState& x, float u, const QI
     T.off[1] = fma_(h2 * h2, T.d2, T.off[0]);
     T.off[2] = fma_(P.b4, T.d2, P.a4 * x.w);
     const float u3 = qb<3>(u);
-    const float fu = P.cf_m * u3, fe = P.cf_m * (x.f - u3);
+    T.df = P.direct ? 0.f : x.f - u3;
+    const float fu = P.cf_m * u3, fe = P.cf_m * T.df;
 #pragma unroll
     for (int s = 0; s < 4; ++s) T.a[s] = fma_(fe, P.p[s], fu);
 }
@@ -480,8 +483,7 @@ __device__ __forceinline__ void q_id_step(QIdState& x, float u, const QId& P, fl
                 a3 = q_id_acc(s[1], c[1], T.a[2], P, j), a4 = q_id_acc(s[2], c[2], T.a[3], P, j);
     x.a += fma_(P.al, x.w, P.be * T.d2);
     x.w += fma_(P.ga, x.w, P.de * T.d2);
-    const float u3 = qb<3>(u);
-    x.f = fma_(x.f - u3, P.pf, u3);
+    x.f = fma_(T.df, P.pf, qb<3>(u));
     q_advance_pv(&x.p, &x.v, &x.cp, &x.cv, h, a1, a2, a3, a4);
 }
 

@@ -566,10 +566,11 @@ int held_chunk(const cf_handle* h, int k) {
     return ((chunk + n - 1) / n) * n;
 }
 
-// the packed tiles of the current tile size, where a k-step call's launches use them
-hipError_t tiles_for_steps(cf_handle* h, int k) {
-    const int mode = held_mode(h, held_chunk(h, k));
-    return mode == LM_TILE || mode == LM_WQ ? build_packed_tiles(h, h->tile) : hipSuccess;
+// the packed tiles of the current tile size, where held steps may use them. A call on
+// four lanes a drone builds them too: a later call of another length may take them, and
+// may be recorded into a graph, where nothing can be allocated.
+hipError_t tiles_for_steps(cf_handle* h) {
+    return h->use_wq || h->mode == LM_TILE ? build_packed_tiles(h, h->tile) : hipSuccess;
 }
 
 StepArgs step_args(const cf_handle* h, float* st, const float* cmd, int K, uint32_t* nf) {
@@ -857,7 +858,8 @@ cf_status cf_set_launch_config(cf_handle* h, int32_t use_wq, int32_t tile, int32
     hipSetDevice(h->device);
     apply_choice(h, use_wq & 1, tile, chunk, (use_wq >> 1) & 1);
     h->wq_waves = wq_waves;
-    return note(h, build_tiles(h, h->tile));
+    const hipError_t e = build_tiles(h, h->tile);
+    return note(h, e == hipSuccess ? tiles_for_steps(h) : e);
 }
 
 cf_status cf_launch_times(cf_handle* h, int32_t slot, float* ms, int32_t max_n, int32_t* n) {
@@ -944,7 +946,7 @@ static cf_status enqueue_steps(cf_handle* h, float* state, const float* cmd, int
         h->timers[1].n = 0;
     }
     // built before any graph capture by cf_step_k, so this returns at once there
-    if ((e = tiles_for_steps(h, k)) != hipSuccess) return note(h, e);
+    if ((e = tiles_for_steps(h)) != hipSuccess) return note(h, e);
     if (plain) {
         const int n = h->ctrl_every;
         // one step per launch; with a slower onboard controller, one controller
@@ -1012,7 +1014,7 @@ cf_status cf_step_k(cf_handle* h, float* state, const float* cmd, int32_t k, uin
         return CF_EINVAL;
     if (nf && check_dev(nf, (size_t)h->M * sizeof(uint32_t))) return CF_EINVAL;
     hipSetDevice(h->device);
-    hipError_t e = tiles_for_steps(h, k);
+    hipError_t e = tiles_for_steps(h);
     if (e != hipSuccess) return note(h, e);
     const int plain = (h->flags & CF_F_PLAIN_KERNEL) ? 1 : 0;
     if (!(h->flags & CF_F_GRAPH)) return enqueue_steps(h, state, cmd, k, nf, h->stream, plain);
@@ -1260,7 +1262,9 @@ cf_status cf_rollout(cf_handle* h, const float* x0, const float* cmds, int32_t T
     if (h->D > 0) {
         const bool quad = quad_roll(h, obj);
         const int mode = roll_mode(h);
-        if (!quad && mode == LM_TILE && (e = build_tiles(h, h->tile)) != hipSuccess) return note(h, e);
+        // (for four lanes a drone too: a later call, or this rollout's backward, may need
+        // them where nothing can be allocated)
+        if (mode == LM_TILE && (e = build_tiles(h, h->tile)) != hipSuccess) return note(h, e);
         e = per_model(h, h->stream, h->split, [&](int models, const int4* tiles, int nt, hipStream_t st, int) {
             KernelSel ks = selection(h, mode, mode == LM_LANE ? 64 : h->tile);
             ks.models = models;
@@ -1397,7 +1401,9 @@ static cf_status rollout_backward_impl(cf_handle* h, const float* cmds, int32_t 
     a.mlp_rec = (g_gain && Hp > 0) ? sc.rec : nullptr;
     if (h->D > 0) {
         const int mode = roll_mode(h);
-        if (!quad && mode == LM_TILE && (e = build_tiles(h, h->tile)) != hipSuccess) return note(h, e);
+        // (for four lanes a drone too: a later call, or this rollout's backward, may need
+        // them where nothing can be allocated)
+        if (mode == LM_TILE && (e = build_tiles(h, h->tile)) != hipSuccess) return note(h, e);
         e = per_model(h, h->stream, h->split, [&](int models, const int4* tiles, int nt, hipStream_t st, int) {
             KernelSel ks = selection(h, mode, mode == LM_LANE ? 64 : h->tile);
             ks.models = models;

@@ -390,8 +390,10 @@ cf_status cf_rollout_backward(cf_handle* h, const float* x0, const float* cmds, 
  * A request whose scratch exceeds the array returns CF_EINVAL before any work:
  * it needs (T + 1) * 6 floats with a figure-eight objective, plus
  * (min(K, T) + 1{reward}) * S * D floats when that is more than one state, plus
- * 52 * D + n_gains * 52 * min(1024, ceil(D / 2048)) floats with g_gain, each
- * rounded up to 64 floats. Every call on one GPU uses the same array, so calls
+ * 52 * D + n_gains * 52 * min(1024, ceil(D / 512)) floats with the g_gain of
+ * linear feedback, or (17 + 4 H) * T * D + n_gains * CF_MLP_PARAMS(H) *
+ * min(1024, ceil(T * D / 2048)) with that of policies, each product rounded up
+ * to 64 floats. Every call on one GPU uses the same array, so calls
  * that overlap on one GPU (other streams, other handles, other threads) race;
  * nothing in it needs to start at zero.
  */

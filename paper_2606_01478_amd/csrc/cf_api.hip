@@ -118,7 +118,6 @@ __global__ __launch_bounds__(256) void k_reduce_world(const float* __restrict__ 
 // component rather than one for all of them: the 52 trees one after the other, and the
 // serial sum over hundreds of chunks, took 108 us for 63 000 drones.
 constexpr int GAIN_COMP = 52;
-constexpr int MLP_MAX_BLOCKS = 1024;
 
 __global__ __launch_bounds__(1024) void k_sum_drones(const float* __restrict__ v, int64_t D,
                                                      const int32_t* __restrict__ drone_world,
@@ -1337,7 +1336,7 @@ static cf_status rollout_backward_impl(cf_handle* h, const float* cmds, int32_t 
     const size_t n_all = (size_t)(T + 1) * h->S * Dm;
     bool seg_all = quad_b && K > 1 && T > K && T >= 16 && n_all <= QUAD_SEG_FLOATS && (T + K - 1) / K <= 65535;
     const int64_t N_rec = (int64_t)T * Dm;
-    const int nb_mlp = (int)std::max<int64_t>(1, std::min<int64_t>((N_rec + 2047) / 2048, MLP_MAX_BLOCKS));
+    const int nb_mlp = cfh::policy_blocks(N_rec);
     const size_t n_ggc = (g_gain && Hp == 0) ? (size_t)52 * Dm : 0;
     // policies: records of every drone-step, or (quad kernels) each drone's own sum of
     // its weight gradient where that is less
@@ -1359,7 +1358,11 @@ static cf_status rollout_backward_impl(cf_handle* h, const float* cmds, int32_t 
     if (noalloc) {
         float* base = scratch_of(h->device);
         if (!base) return CF_EUNSUPPORTED;
-        // sizes beyond the array are refused before any work
+        // sizes beyond the array are refused before any work; the slices below add up to no
+        // more than what is asked for
+        const cfh::BackwardShape shape{T, K, h->S, h->D, kind == CF_OBJ_BPTT_REWARD, obj && !obj->ref_table, Hp,
+                                       g_gain ? h->n_gains : 0};
+        if (cfh::noalloc_floats(shape) > cap) return CF_EINVAL;
         if (up(n_tab) + up(n_seg) + up(n_ggc) + up(n_rec) + up(n_part) > cap) return CF_EINVAL;
         float* q = base;
         auto take = [&](size_t n) -> float* {

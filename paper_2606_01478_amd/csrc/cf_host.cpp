@@ -221,6 +221,23 @@ int sum_chunks(int64_t D) {
     return (int)std::max<int64_t>(1, (D + chunk - 1) / chunk);
 }
 
+int policy_blocks(int64_t records) {
+    return (int)std::max<int64_t>(1, std::min<int64_t>((records + 2047) / 2048, 1024));
+}
+
+size_t noalloc_floats(const BackwardShape& b) {
+    const auto up = [](int64_t n) { return (size_t)((n + 63) / 64 * 64); };
+    const int64_t D = std::max<int64_t>(b.D, 1), records = (int64_t)b.T * D;
+    const int64_t slots = std::min(b.K, b.T) + (b.reward ? 1 : 0);
+    size_t n = up(b.eight ? (int64_t)(b.T + 1) * 6 : 0) + up(slots > 1 ? slots * b.S * D : 0);
+    if (b.gains > 0 && b.hidden > 0)
+        n += up((17 + 4 * (int64_t)b.hidden) * records) +
+             up((int64_t)b.gains * policy_blocks(records) * CF_MLP_PARAMS(b.hidden));
+    else if (b.gains > 0)
+        n += up(52 * D) + up((int64_t)b.gains * 52 * std::min<int64_t>(1024, (D + 511) / 512));
+    return n;
+}
+
 size_t sum_part_floats(int n_gains, int nc, int64_t D) { return (size_t)n_gains * nc * sum_chunks(D); }
 
 namespace {

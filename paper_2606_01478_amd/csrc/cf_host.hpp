@@ -78,6 +78,24 @@ int sum_chunks(int64_t D);
 // floats of the partial sums of nc components per gain
 size_t sum_part_floats(int n_gains, int nc, int64_t D);
 
+// ---- scratch of a rollout's backward -----------------------------------------------
+
+// What of a backward call decides its scratch: reward: the reward objective; eight: a
+// figure-eight objective; hidden: width of its policies (0: linear feedback or none);
+// gains: 0 when no gain gradient is asked for.
+struct BackwardShape {
+    int T, K, S;
+    int64_t D;
+    bool reward, eight;
+    int hidden, gains;
+};
+// Floats of the static scratch that cf_rollout_backward_noalloc asks for (the sum that its
+// contract states, each term rounded up to 64). The layouts that the kernels of a batch
+// use take no more, so what is refused does not depend on them.
+size_t noalloc_floats(const BackwardShape& b);
+// workgroups of the sum over a policy's records
+int policy_blocks(int64_t records);
+
 // ---- autotune cache ---------------------------------------------------------------
 
 struct LaunchChoice {

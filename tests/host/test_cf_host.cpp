@@ -2,6 +2,7 @@
 // descriptor validation, derived records, tile lists, the autotune cache file
 // and the checkpoint tags. Built with AddressSanitizer and UBSan by
 // tests/test_host_sanitized.py; exits non-zero on the first failed check.
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
@@ -325,6 +326,29 @@ static void test_sum_chunks() {
     CHECK(cfh::sum_chunks(63000) == 4);
 }
 
+// the sum that the allocation-free backward's contract states, and that the slices of
+// either layout of the gradient sums fit in it
+static void test_noalloc_floats() {
+    const auto up = [](int64_t n) { return (n + 63) / 64 * 64; };
+    CHECK(cfh::noalloc_floats({50, 10, 25, 1000, false, false, 0, 0}) == (size_t)up(10 * 25 * 1000));
+    CHECK(cfh::noalloc_floats({50, 1, 25, 1000, false, false, 0, 0}) == 0);
+    CHECK(cfh::noalloc_floats({50, 1, 25, 1000, true, true, 0, 0}) == (size_t)(up(51 * 6) + up(2 * 25 * 1000)));
+    CHECK(cfh::noalloc_floats({8, 20, 13, 1025, false, true, 0, 2}) ==
+          (size_t)(up(9 * 6) + up(8 * 13 * 1025) + up(52 * 1025) + up(2 * 52 * 3)));
+    CHECK(cfh::noalloc_floats({40, 8, 13, 16, true, true, 16, 1}) ==
+          (size_t)(up(41 * 6) + up(9 * 13 * 16) + up(81 * 40 * 16) + up(1 * 1 * CF_MLP_PARAMS(16))));
+    CHECK(cfh::noalloc_floats({4, 4, 13, 0, false, false, 0, 3}) == (size_t)(up(4 * 13) + 64 + 192));
+    for (int64_t D : {1, 511, 16385, 32768, 300000})
+        for (int gains : {1, 7, 1000}) {
+            CHECK(cfh::sum_part_floats(gains, 52, D) <= (size_t)gains * 52 * std::min<int64_t>(1024, (D + 511) / 512));
+            for (int H : {1, 8, 16})
+                for (int T : {1, 9, 100})
+                    if (CF_MLP_PARAMS(H) <= (17 + 4 * H) * T)   // each drone's own sum, where that is less
+                        CHECK(cfh::sum_part_floats(gains, CF_MLP_PARAMS(H), D) <=
+                              (size_t)gains * cfh::policy_blocks(T * D) * CF_MLP_PARAMS(H));
+        }
+}
+
 int main(int argc, char** argv) {
     const std::string dir = argc > 1 ? argv[1] : "/tmp";
     test_validate_desc();
@@ -334,6 +358,7 @@ int main(int argc, char** argv) {
     test_cache(dir);
     test_tags();
     test_sum_chunks();
+    test_noalloc_floats();
     std::printf("host tests passed: %d checks\n", g_checks);
     return 0;
 }

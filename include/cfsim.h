@@ -237,7 +237,8 @@ typedef struct cf_objective {
  * policies and each lane's activations live in LDS), and the handle's tile
  * size must be 64 lanes when its worlds are tiled (CF_EUNSUPPORTED otherwise).
  * The backward keeps (17 + 4 H) floats per drone-step of scratch for the
- * weight-gradient reduction.
+ * weight-gradient reduction; a small batch with H <= 16 (four lanes a drone, see
+ * cf_rollout_backward) CF_MLP_PARAMS(H) floats per drone where that is less.
  */
 #define CF_MLP_MAX_HIDDEN 32
 #define CF_MLP_PARAMS(H) (13 * (H) + (H) + (H) * (H) + (H) + 4 * (H) + 4)
@@ -368,7 +369,13 @@ cf_status cf_rollout(cf_handle* h, const float* x0, const float* cmds, int32_t T
  * a buffer overwritten since (by another handle's forward, or reused memory)
  * makes the kernel write NaN to every requested output and sets the handle's
  * sticky status to CF_ESTATE, reported by cf_last_error. Any number of
- * forwards may precede their backwards. Outputs (overwritten, each may be
+ * forwards may precede their backwards. Scratch: the handle keeps, grown on
+ * demand until it is destroyed, the recomputed states of one segment (min(K, T) *
+ * S * D floats). A batch of one model that is small enough to run four lanes a
+ * drone (128 drones per compute unit) recomputes its segments side by side, and
+ * then keeps all (T + 1) * S * D floats of them where that is at most 256 MiB and
+ * can be had, whatever K is. With g_gain it keeps 52 * D floats (linear feedback), or
+ * what CF_MLP_PARAMS states for policies, and the partial sums. Outputs (overwritten, each may be
  * NULL): g_cmds device [T][4][D] (d/d ubar_t), g_x0 device [S][D], g_gain
  * device [n_gains][4][13] (sum over drones in a fixed order; requires
  * obj->gain). Errors: CF_EINVAL (sizes as in cf_rollout, NULL ckpt, g_gain

@@ -1351,7 +1351,8 @@ static cf_status rollout_backward_impl(cf_handle* h, const float* cmds, int32_t 
     const size_t cap = CF_NOALLOC_SCRATCH_BYTES / sizeof(float);
     seg_all = seg_all && quad &&
               (!noalloc || up(n_tab) + up(n_all) + up(n_ggc) + up(n_rec) + up(n_part) <= cap);
-    const size_t n_seg = seg_all ? n_all : (slots > 1 ? (size_t)slots * h->S * Dm : 0);
+    const size_t n_slots = slots > 1 ? (size_t)slots * h->S * Dm : 0;
+    size_t n_seg = seg_all ? n_all : n_slots;
     hipSetDevice(h->device);
     hipError_t e;
     BwdScratch sc;
@@ -1377,7 +1378,19 @@ static cf_status rollout_backward_impl(cf_handle* h, const float* cmds, int32_t 
         sc.rec = take(n_rec);
         sc.gpart = take(n_part);
     } else {
-        if (n_seg && (e = ensure(h->seg, n_seg * sizeof(float))) != hipSuccess) return note(h, e);
+        if (n_seg) {
+            // where the memory for every segment at once is not to be had, one at a time
+            size_t got = 0;
+            const auto grow = [&](size_t n) { return ensure(h->seg, n * sizeof(float)); };
+            e = seg_all ? cfh::grow_to_any({n_all, std::max<size_t>(n_slots, 1)}, hipErrorOutOfMemory, &got, grow)
+                        : grow(n_seg);
+            if (got > 0) {
+                (void)hipGetLastError();
+                seg_all = false;
+                n_seg = n_slots;
+            }
+            if (e != hipSuccess) return note(h, e);
+        }
         if (n_ggc && (e = ensure(h->ggc, n_ggc * sizeof(float))) != hipSuccess) return note(h, e);
         if (n_rec && (e = ensure(h->rec, n_rec * sizeof(float))) != hipSuccess) return note(h, e);
         if (n_part && (e = ensure(h->gpart, n_part * sizeof(float))) != hipSuccess) return note(h, e);

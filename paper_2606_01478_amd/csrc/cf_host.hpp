@@ -6,6 +6,7 @@
 // test builds it on its own under AddressSanitizer and UBSan.
 #pragma once
 #include <cstdint>
+#include <initializer_list>
 #include <map>
 #include <string>
 #include <vector>
@@ -95,6 +96,21 @@ struct BackwardShape {
 size_t noalloc_floats(const BackwardShape& b);
 // workgroups of the sum over a policy's records
 int policy_blocks(int64_t records);
+
+// Tries the sizes in order (most wanted first) with grow(size), a status of which
+// `too_large` moves on to the next size and any other ends the search. *got receives the
+// index of the last size tried; returns its status.
+template <class Status, class Grow>
+Status grow_to_any(std::initializer_list<size_t> sizes, Status too_large, size_t* got, Grow&& grow) {
+    Status s = too_large;
+    *got = 0;
+    for (size_t n : sizes) {
+        s = grow(n);
+        if (s != too_large || *got + 1 == sizes.size()) break;
+        ++*got;
+    }
+    return s;
+}
 
 // ---- autotune cache ---------------------------------------------------------------
 

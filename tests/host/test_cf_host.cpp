@@ -349,6 +349,22 @@ static void test_noalloc_floats() {
         }
 }
 
+// the first size that can be had; other errors are not retried
+static void test_grow_to_any() {
+    enum { OK, FULL, BROKEN };
+    size_t got = 9, limit = 0;
+    int calls = 0;
+    const auto grow = [&](size_t n) { ++calls; return n <= limit ? OK : FULL; };
+    limit = 100;
+    CHECK(cfh::grow_to_any({(size_t)100, (size_t)10}, FULL, &got, grow) == OK && got == 0 && calls == 1);
+    limit = 99;
+    CHECK(cfh::grow_to_any({(size_t)100, (size_t)10}, FULL, &got, grow) == OK && got == 1 && calls == 3);
+    limit = 9;
+    CHECK(cfh::grow_to_any({(size_t)100, (size_t)10}, FULL, &got, grow) == FULL && got == 1 && calls == 5);
+    CHECK(cfh::grow_to_any({(size_t)100, (size_t)10}, FULL, &got, [&](size_t) { ++calls; return BROKEN; }) == BROKEN);
+    CHECK(got == 0 && calls == 6);
+}
+
 int main(int argc, char** argv) {
     const std::string dir = argc > 1 ? argv[1] : "/tmp";
     test_validate_desc();
@@ -359,6 +375,7 @@ int main(int argc, char** argv) {
     test_tags();
     test_sum_chunks();
     test_noalloc_floats();
+    test_grow_to_any();
     std::printf("host tests passed: %d checks\n", g_checks);
     return 0;
 }

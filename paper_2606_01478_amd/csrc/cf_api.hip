@@ -1261,9 +1261,9 @@ cf_status cf_rollout(cf_handle* h, const float* x0, const float* cmds, int32_t T
     if (h->D > 0) {
         const bool quad = quad_roll(h, obj);
         const int mode = roll_mode(h);
-        // (for four lanes a drone too: a later call, or this rollout's backward, may need
-        // them where nothing can be allocated)
-        if (mode == LM_TILE && (e = build_tiles(h, h->tile)) != hipSuccess) return note(h, e);
+        // (the lists of the current tile size are there since the handle or the launch
+        // choice was made)
+        if (!quad && mode == LM_TILE && (e = build_tiles(h, h->tile)) != hipSuccess) return note(h, e);
         e = per_model(h, h->stream, h->split, [&](int models, const int4* tiles, int nt, hipStream_t st, int) {
             KernelSel ks = selection(h, mode, mode == LM_LANE ? 64 : h->tile);
             ks.models = models;
@@ -1417,9 +1417,9 @@ static cf_status rollout_backward_impl(cf_handle* h, const float* cmds, int32_t 
     a.mlp_rec = (g_gain && Hp > 0) ? sc.rec : nullptr;
     if (h->D > 0) {
         const int mode = roll_mode(h);
-        // (for four lanes a drone too: a later call, or this rollout's backward, may need
-        // them where nothing can be allocated)
-        if (mode == LM_TILE && (e = build_tiles(h, h->tile)) != hipSuccess) return note(h, e);
+        // (the lists of the current tile size are there since the handle or the launch
+        // choice was made)
+        if (!quad && mode == LM_TILE && (e = build_tiles(h, h->tile)) != hipSuccess) return note(h, e);
         e = per_model(h, h->stream, h->split, [&](int models, const int4* tiles, int nt, hipStream_t st, int) {
             KernelSel ks = selection(h, mode, mode == LM_LANE ? 64 : h->tile);
             ks.models = models;

@@ -162,12 +162,87 @@ __global__ __launch_bounds__(64) void k_sum_parts(const float* __restrict__ part
     if (threadIdx.x == 0) g[blockIdx.x] = s;
 }
 
+// The same sums for many gains: a workgroup takes one gain (y) and up to 52 components
+// (z) of its chunk. It looks every drone's gain up once, lists the drones whose gain is
+// k, and each wave then sums its components over the list, a drone a lane. Component by
+// component the look-ups alone are 52 times gains times drones. Of more than SUM_FEW
+// gains, component by component -> so:
+//   1024 worlds of a drone, a gain each: 151 -> 20 us; 4096 of one: 888 -> 76;
+//   256 of 460 drones, 64 gains 377 -> 27, 256: 1453 -> 52; 32 768 of 14, 16: 528 -> 58.
+// Of few the other is faster, with a workgroup for every component: 4096 worlds of 16
+// drones, 1 gain 12 against 459 us, 4: 23 against 130, 16: 51 against 48; 4096 of one, 16
+// gains 3 against 10, 64: 15 against 6.
+constexpr int SUM_FEW = 16;
+__global__ __launch_bounds__(1024) void k_sum_drones_by_gain(const float* __restrict__ v, int nc, int64_t D,
+                                                             const int32_t* __restrict__ drone_world,
+                                                             const int32_t* __restrict__ gidx, int64_t chunk,
+                                                             float* __restrict__ out) {
+    constexpr int PIECE = 16384, WAVES = 16, PER_WAVE = (GAIN_COMP + WAVES - 1) / WAVES;
+    __shared__ uint16_t list[PIECE];
+    __shared__ int counts[WAVES];
+    const int b = blockIdx.x, nb = gridDim.x, k = blockIdx.y, c0 = blockIdx.z * GAIN_COMP;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, n = min(GAIN_COMP, nc - c0);
+    const int64_t lo = b * chunk, hi = min(D, lo + chunk);
+    float acc[PER_WAVE];
+#pragma unroll
+    for (int q = 0; q < PER_WAVE; ++q) acc[q] = 0.f;
+    for (int64_t base = lo; base < hi; base += PIECE) {
+        // 16 drones a thread, their look-ups at once so that they overlap
+        const int64_t d0 = base + threadIdx.x;
+        int w[16];
+        uint32_t mine = 0;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) w[i] = drone_world[min(d0 + i * 1024, hi - 1)];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) w[i] = gidx[w[i]];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) mine |= (w[i] == k && d0 + i * 1024 < hi ? 1u : 0u) << i;
+        int at = __popc(mine);
+#pragma unroll
+        for (int h = 1; h < 64; h <<= 1) {
+            const int u = __shfl_up(at, h, 64);
+            if (lane >= h) at += u;
+        }
+        if (lane == 63) counts[wave] = at;
+        at -= __popc(mine);
+        __syncthreads();
+        int m = 0;
+#pragma unroll
+        for (int i = 0; i < WAVES; ++i) {
+            at += i < wave ? counts[i] : 0;
+            m += counts[i];
+        }
+        for (; mine; mine &= mine - 1) list[at++] = (uint16_t)(threadIdx.x + (__ffs(mine) - 1) * 1024);
+        __syncthreads();
+#pragma unroll 4
+        for (int j = lane; j < m; j += 64) {
+            const float* const x = v + (size_t)c0 * D + base + list[j];
+            // (past the last component: read again and dropped)
+#pragma unroll
+            for (int q = 0; q < PER_WAVE; ++q) acc[q] += x[(size_t)min(wave + q * WAVES, n - 1) * D];
+        }
+        __syncthreads();   // counts and list are free again
+    }
+#pragma unroll
+    for (int q = 0; q < PER_WAVE; ++q) {
+        float s = acc[q];
+#pragma unroll
+        for (int h = 32; h > 0; h >>= 1) s += __shfl_down(s, h, 64);
+        const int c = wave + q * WAVES;
+        if (lane == 0 && c < n) out[((size_t)k * nc + c0 + c) * nb + b] = s;
+    }
+}
+
 // part: cfh::sum_part_floats(n_gains, nc, D) floats (unused with one chunk)
 static hipError_t sum_drones(const float* v, int nc, int64_t D, const int32_t* drone_world, const int32_t* gidx,
                              int n_gains, float* part, float* g, hipStream_t s) {
     const unsigned nb = (unsigned)cfh::sum_chunks(D);
-    hipLaunchKernelGGL(k_sum_drones, dim3(nb, nc, n_gains), dim3(1024), 0, s, v, D, drone_world, gidx, n_gains,
-                       cfh::sum_chunk(D), nb == 1 ? g : part);
+    if (n_gains <= SUM_FEW)
+        hipLaunchKernelGGL(k_sum_drones, dim3(nb, nc, n_gains), dim3(1024), 0, s, v, D, drone_world, gidx, n_gains,
+                           cfh::sum_chunk(D), nb == 1 ? g : part);
+    else
+        hipLaunchKernelGGL(k_sum_drones_by_gain, dim3(nb, n_gains, (nc + GAIN_COMP - 1) / GAIN_COMP), dim3(1024), 0, s,
+                           v, nc, D, drone_world, gidx, cfh::sum_chunk(D), nb == 1 ? g : part);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || nb == 1) return e;
     hipLaunchKernelGGL(k_sum_parts, dim3((unsigned)(n_gains * nc)), dim3(64), 0, s, part, (int)nb, g);

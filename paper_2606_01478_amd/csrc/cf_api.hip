@@ -611,6 +611,7 @@ KernelSel selection(const cf_handle* h, int mode, int tile) {
     ks.mode = mode;
     ks.tile = tile;
     ks.aero = h->aero;
+    ks.shared = h->models == MS_BOTH;
     return ks;
 }
 

@@ -39,6 +39,7 @@ struct KernelSel {
     int mode;    // LM_*
     int tile;    // lanes per workgroup (64, 128, 256)
     int aero;    // kernels with gyroscopic/reaction torques, drag and the general rotor law compiled in
+    int shared;  // launches of both models run side by side
 };
 
 struct StepArgs {

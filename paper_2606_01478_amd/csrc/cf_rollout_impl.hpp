@@ -1038,12 +1038,15 @@ __global__ __launch_bounds__(256, (lane_in_lds<BWD, MODELS, CTRL, INTEG, AERO, E
     else rollout_drone<BWD, MODEL_ID, CTRL, INTEG, AERO, EXT>(rec, a, d, w, S_h, G, gl, gs);
 }
 
-// Identified drones are held to four waves per SIMD (128 registers, a few spilled):
-// their adjoint shares the compute units with the first-principles one, whose 235
-// registers leave room for no wider wave (118 000 uneven drones, 250 steps, both
-// models, forward and adjoint, before rows took scalar bases: 3047 us, unbounded 3125).
-template <bool BWD, int MODELS, int CTRL, int INTEG, bool AERO, bool EXT>
-__global__ __launch_bounds__(256, (MODELS == MS_ID && !EXT && !AERO) ? 4 : 1) void k_rollout_tile(
+// WAVES: waves per SIMD that the registers are held to. Identified drones forward to four
+// (128 registers, a few spilled): 256 worlds of 4000, 10 steps 109 us, unbounded 122; 70 of
+// 500, 40 steps 60 either way. Their adjoint to four where it shares the compute units with
+// the first-principles one, whose 235 registers leave room for no wider wave (118 000
+// uneven drones of both models, 250 steps, forward and adjoint: 2480 us, unbounded 3000);
+// alone it is faster unbounded (70 worlds of 500 drones, 40 steps 168 us, bounded 217; 256
+// of 4000, 10 steps 436, bounded 491).
+template <bool BWD, int MODELS, int CTRL, int INTEG, bool AERO, bool EXT, int WAVES>
+__global__ __launch_bounds__(256, WAVES) void k_rollout_tile(
     RollArgs a, const int4* __restrict__ tiles, int S_h) {
     rollout_priority();
     const int4 td = tiles[blockIdx.x];
@@ -1108,8 +1111,13 @@ static hipError_t launch_roll_k(const KernelSel& ks, const RollArgs& a, const in
         }
     } else {
         const size_t lds = roll_lds_bytes<BWD, EXT>(a, ks.tile);
-        hipLaunchKernelGGL((k_rollout_tile<BWD, MODELS, CTRL, INTEG, AERO, EXT>), dim3(n_tiles), dim3(ks.tile), lds,
-                           s, a, tiles, S_h);
+        constexpr bool BOUND = MODELS == MS_ID && !EXT && !AERO;
+        if (BOUND && (!BWD || ks.shared))
+            hipLaunchKernelGGL((k_rollout_tile<BWD, MODELS, CTRL, INTEG, AERO, EXT, BOUND ? 4 : 1>), dim3(n_tiles),
+                               dim3(ks.tile), lds, s, a, tiles, S_h);
+        else
+            hipLaunchKernelGGL((k_rollout_tile<BWD, MODELS, CTRL, INTEG, AERO, EXT, (BOUND && !BWD) ? 4 : 1>),
+                               dim3(n_tiles), dim3(ks.tile), lds, s, a, tiles, S_h);
     }
     return hipGetLastError();
 }

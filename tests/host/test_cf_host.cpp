@@ -365,10 +365,97 @@ static void test_grow_to_any() {
     CHECK(got == 0 && calls == 6);
 }
 
+// stage values (y[0..3]) and the step (y[4]) of classical RK4 of y' = -c y from y = 1
+static void rk4_lag(double c, double h, double* y) {
+    y[0] = 1.0;
+    y[1] = 1.0 + h / 2 * (-c * y[0]);
+    y[2] = 1.0 + h / 2 * (-c * y[1]);
+    y[3] = 1.0 + h * (-c * y[2]);
+    y[4] = 1.0 + h / 6 * -c * (y[0] + 2 * y[1] + 2 * y[2] + y[3]);
+}
+
+// the closed forms of the RK4 step's coefficients against RK4 itself in binary64
+static void test_derive_step() {
+    const auto near = [](double a, double b, double scale) { return std::fabs(a - b) <= 4e-7 * scale; };
+    for (float dt : {0.0005f, 0.002f, 0.02f}) {
+        DescFixture f;
+        float* r = f.params.data();
+        r[CF_P_THRUST] = 1e-3f; r[CF_P_THRUST + 1] = 2e-6f;
+        for (int j = 0; j < 3; ++j) r[CF_P_TORQUE + j] = 0.006f * r[CF_P_THRUST + j];
+        const float tx[4] = {-0.03f, -0.02f, 0.03f, 0.025f}, ty[4] = {-0.03f, 0.02f, 0.03f, -0.01f};
+        for (int i = 0; i < 4; ++i) { r[CF_P_MIX_TX + i] = tx[i]; r[CF_P_MIX_TY + i] = ty[i]; }
+        r[CF_P_MOTOR_UP] = r[CF_P_MOTOR_DOWN] = 33.f;
+        float o[cfk::NREC];
+        cfh::derive_record(r, o);
+        cfh::derive_step(CF_MODEL_FP, dt, o);
+        double y[5];
+        rk4_lag(r[CF_P_MOTOR_UP], dt, y);
+        CHECK(near(o[cfk::F_P2], y[1], 1) && near(o[cfk::F_P4], y[3], 1) && near(o[cfk::F_PF], y[4], 1));
+        CHECK(near(o[cfk::F_Q2], 1 - y[1], 1 - y[1]) && near(o[cfk::F_Q4], 1 - y[3], 1 - y[3]));
+        CHECK(near(o[cfk::F_QF], 1 - y[4], 1 - y[4]));
+        // stage 3 of any quadratic in the stage value
+        for (int p = 0; p < 3; ++p)
+            CHECK(near(o[cfk::F_L1] + o[cfk::F_L2] * std::pow(y[1], p) + o[cfk::F_L4] * std::pow(y[3], p),
+                       std::pow(y[2], p), 1));
+        // twice the specific thrust and the angular accelerations of four rotor speeds
+        const double d[4] = {-150.0, 40.0, 0.0, 700.0}, J[3] = {r[CF_P_J], r[CF_P_J + 1], r[CF_P_J + 2]};
+        double F = 0, T[3] = {0, 0, 0}, a2 = o[cfk::F_A2R], t[3] = {o[cfk::F_TR], o[cfk::F_TR + 1], o[cfk::F_TR + 2]};
+        double size[3] = {0, 0, 0};
+        for (int i = 0; i < 4; ++i) {
+            const double W = (double)o[cfk::D_WR] + d[i];
+            const double fi = r[CF_P_THRUST] + W * (r[CF_P_THRUST + 1] + W * r[CF_P_THRUST + 2]);
+            const double qi = r[CF_P_TORQUE] + W * (r[CF_P_TORQUE + 1] + W * r[CF_P_TORQUE + 2]);
+            const double m3[3] = {r[CF_P_MIX_TX + i] * fi, r[CF_P_MIX_TY + i] * fi, r[CF_P_MIX_YAW + i] * qi};
+            const double dd = d[i] * (o[cfk::F_K1] + o[cfk::F_K2] * d[i]);
+            F += fi;
+            a2 += dd;
+            t[0] += o[cfk::F_TX + i] * dd; t[1] += o[cfk::F_TY + i] * dd; t[2] += o[cfk::F_TZ + i] * dd;
+            for (int a = 0; a < 3; ++a) { T[a] += m3[a]; size[a] += std::fabs(m3[a]) / J[a]; }
+        }
+        CHECK(near(a2, 2 * F / r[CF_P_MASS], a2));
+        for (int a = 0; a < 3; ++a) CHECK(near(t[a], T[a] / J[a], 4 * size[a]));
+        CHECK(near(o[cfk::F_DJ], (J[2] - J[1]) / J[0], 1) && near(o[cfk::F_DJ + 1], (J[0] - J[2]) / J[1], 1) &&
+              near(o[cfk::F_DJ + 2], (J[1] - J[0]) / J[2], 1));
+
+        for (float ctau : {33.f, 0.f}) {
+            float* q = f.params.data() + CF_NPARAM;
+            q[CF_P_CTAU] = ctau;
+            for (int i = 0; i < 3; ++i) {
+                q[CF_P_CPSI1 + i] = -150.f - 20.f * i;
+                q[CF_P_CPSI2 + i] = -18.f + 3.f * i;
+                q[CF_P_CPSI3 + i] = 140.f;
+            }
+            cfh::derive_record(q, o);
+            cfh::derive_step(CF_MODEL_ID, dt, o);
+            rk4_lag(ctau, dt, y);
+            for (int s = 0; s < 5; ++s) {
+                const double want = ctau == 0.f ? 0.0 : y[s];   // no dynamics: the command at every stage
+                CHECK(near(s < 4 ? o[cfk::I_P + s] : o[cfk::I_PF], want, 1));
+                CHECK(near(s < 4 ? o[cfk::I_Q + s] : o[cfk::I_QF], 1 - want, 1));
+            }
+            for (int i = 0; i < 3; ++i) {
+                const double c1 = q[CF_P_CPSI1 + i], c2 = q[CF_P_CPSI2 + i], c3 = q[CF_P_CPSI3 + i], h = dt;
+                const double a0 = 0.3, w0 = -1.7, u = 0.2;
+                const auto acc = [&](double a, double w) { return c1 * a + c2 * w + c3 * u; };
+                const double k1 = w0, l1 = acc(a0, w0);
+                const double k2 = w0 + h / 2 * l1, l2 = acc(a0 + h / 2 * k1, w0 + h / 2 * l1);
+                const double k3 = w0 + h / 2 * l2, l3 = acc(a0 + h / 2 * k2, w0 + h / 2 * l2);
+                const double k4 = w0 + h * l3, l4 = acc(a0 + h * k3, w0 + h * l3);
+                const double scale = h * (std::fabs(w0) + std::fabs(l1) * h);
+                CHECK(near(o[cfk::I_AL + i] * w0 + o[cfk::I_BE + i] * l1, h / 6 * (k1 + 2 * k2 + 2 * k3 + k4), scale));
+                CHECK(near(o[cfk::I_A4 + i] * w0 + o[cfk::I_B4 + i] * l1, h * k3, scale));
+                CHECK(near(o[cfk::I_GA + i] * w0 + o[cfk::I_DE + i] * l1, h / 6 * (l1 + 2 * l2 + 2 * l3 + l4),
+                           h * (std::fabs(l1) + 200 * std::fabs(w0))));
+            }
+        }
+    }
+}
+
 int main(int argc, char** argv) {
     const std::string dir = argc > 1 ? argv[1] : "/tmp";
     test_validate_desc();
     test_derive_record();
+    test_derive_step();
     test_tile_list();
     test_packed_tiles();
     test_cache(dir);

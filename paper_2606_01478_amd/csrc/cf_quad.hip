@@ -646,8 +646,9 @@ __global__ __launch_bounds__(64) void k_quad_bwd(RollArgs a) {
     const QLane L{(int)(threadIdx.x & 3u), d, (uint32_t)a.D};
     if (!ckpt_tag_intact(a)) {
         if (L.j == 0) {
-            poison_gradients(a, DroneAt{blockIdx.x * 16u, threadIdx.x & ~3u});
-            if constexpr (U > 0 && U <= 4) {
+            constexpr bool SUMS = U > 0 && U <= 4;   // (below)
+            poison_gradients(a, DroneAt{blockIdx.x * 16u, threadIdx.x & ~3u}, !SUMS);
+            if constexpr (SUMS) {
                 if (a.mlp_rec)
                     for (int i = 0; i < a.mlp_P; ++i) a.mlp_rec[(size_t)i * a.D + d] = __builtin_nanf("");
             }

@@ -949,7 +949,8 @@ __device__ __forceinline__ bool ckpt_tag_intact(const RollArgs& a) {
     return ok;
 }
 
-__device__ __forceinline__ void poison_gradients(const RollArgs& a, const DroneAt& d) {
+// records: RollArgs::mlp_rec holds records of every drone-step
+__device__ __forceinline__ void poison_gradients(const RollArgs& a, const DroneAt& d, bool records = true) {
     const size_t D = (size_t)a.D;
     const float nan = __builtin_nanf("");
     if (a.g_cmds)
@@ -958,6 +959,8 @@ __device__ __forceinline__ void poison_gradients(const RollArgs& a, const DroneA
         for (int i = 0; i < a.S_h; ++i) at(a.g_x0, (size_t)i * D, d) = nan;
     if (a.ggc)
         for (int i = 0; i < NG; ++i) at(a.ggc, (size_t)i * D, d) = nan;
+    if (a.mlp_rec && records)
+        for (size_t i = 0; i < (size_t)(17 + 4 * a.mlp_H) * a.T; ++i) at(a.mlp_rec, i * D, d) = nan;
     atomicOr(a.dflag, 1u);
 }
 

@@ -418,9 +418,9 @@ cf_status cf_rollout_backward_noalloc(cf_handle* h, const float* x0, const float
  * fastest for this handle and store it in the autotune cache file
  * ($CFSIM_AUTOTUNE_CACHE, default $HOME/.cache/cfsim_autotune.txt: one line per
  * handle signature with the chosen shape and its time; the signature is the
- * version of the kernels, the device architecture, worlds, drones, first-principles worlds, interface,
- * integrator, whether drag or rotor inertia is present, and the control
- * interval). Synchronises.
+ * version of the kernels, the device architecture, worlds, drones,
+ * first-principles worlds, interface, integrator, whether drag or rotor inertia
+ * is present, and the control interval). Synchronises.
  */
 cf_status cf_autotune(cf_handle* h, const float* state, const float* cmd, int32_t k, int32_t budget_ms);
 

@@ -1776,9 +1776,10 @@ __device__ __forceinline__ void id_step_base(float* x, float* comp, const float*
 }
 
 // A step on its own, as rollouts and sampled rollouts take it: the start angles' sines and
-// cosines in full. Carried as below they cost their states up to half as much error again
-// (800 drones, rms against binary64, in full -> carried: 2 ms, 500 steps 3.4e-7 -> 4.6e-7;
-// 20 ms, 40 steps 1.6e-7 -> 2.3e-7).
+// cosines in full. Carried as below they cost the states up to 1.8 times the error (800
+// drones with feedback, rms over all rows against binary64, in full -> carried: 2 ms, 500
+// steps 1.0e-7 -> 1.8e-7; 20 ms, 40 steps 6.1e-8 -> 8.8e-8), and they are no faster (1024
+// drones, forward and adjoint of 500 steps 1031 -> 1040 us).
 template <int INTEG>
 __device__ __forceinline__ void id_step(float* x, float* comp, const float* u, const IdParams& P, float dt) {
     EulerBase B;

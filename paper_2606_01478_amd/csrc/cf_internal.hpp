@@ -25,10 +25,10 @@ enum : int { LM_LANE = 0, LM_TILE = 1, LM_WQ = 2, LM_QUAD = 3 };
 //   attitude controller  4096: 123 -> 55 us, 16384: 125 -> 60, 32768: 133 -> 101, 49152: 145 -> 144
 //   rotor interface      4096:  67 -> 40 us, 16384:  69 -> 43, 32768:  72 ->  72, 49152:  75 -> 102
 //   identified           4096:  65 -> 45 us, 16384:  66 -> 55, 32768:  69 ->  68, 49152:  70 ->  92
-// and of rollouts with their adjoint (50 steps, feedback): attitude controller 16384:
-// 457 -> 302 us, 32768: 489 -> 351, 49152: 535 -> 527; identified 16384: 304 -> 243,
-// 32768: 331 -> 296, 65536: 389 -> 455. A single step gains nothing beyond 16 per unit
-// (it is bound by its loads).
+// and of rollouts with their adjoint (50 steps, feedback, checkpoint every 10): attitude
+// controller 16384: 392 -> 233 us, 32768: 444 -> 304, 49152: 468 -> 440, 65536: 479 -> 504;
+// identified 16384: 240 -> 151, 32768: 256 -> 220, 49152: 269 -> 267, 65536: 280 -> 345. A
+// single step gains nothing beyond 16 per unit (it is bound by its loads).
 constexpr size_t QUAD_SEG_FLOATS = (size_t)64 << 20;   // states kept at once by the adjoint: 256 MiB
 constexpr int QUAD_HELD = 64, QUAD_HELD_PID = 128, QUAD_HELD_ONE = 16, QUAD_ROLL = 128;
 

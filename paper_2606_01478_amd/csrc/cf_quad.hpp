@@ -452,7 +452,8 @@ __device__ __forceinline__ void q_id_rebase(float a, QIdBase& b) {
 // component j of a R(Psi) e_z - g e_z from the lane's sine and cosine
 __device__ __forceinline__ float q_id_acc(float s, float c, float a, const QId& P, int j) {
     // lane 0: cps (sth cph) + sps sph, lane 1: sps (sth cph) - cps sph, lane 2: cth cph
-    const float c2 = qperm<2, 2, 1, 3>(c), s2 = qb<2>(s);
+    // (whose zero factor of sps may not meet a yaw that is not finite: sph takes its place)
+    const float c2 = qperm<2, 2, 1, 3>(c), s2 = qperm<2, 2, 0, 3>(s);
     const float al = j == 1 ? s2 : c2, be = j == 1 ? c2 : s2;
     const float X = qb<0>(c) * (j == 2 ? 1.f : qb<1>(s)), Y = qb<0>(s) * P.sy;
     return fma_(a, fma_(al, X, be * Y), -P.g);

@@ -1,0 +1,57 @@
+"""Drones with a non-finite input among others, four lanes a drone and one: what the input
+does not reach stays finite and the same, whichever kernel the batch's size selects. Each
+batch is run as it is and as the first drones of one above the four-lane range."""
+import dataclasses
+
+import numpy as np
+import pytest
+import torch
+
+import workloads as W
+from test_gpu_mlp import _grads
+from test_gpu_parity import _rollout_grads, _sim
+
+pytestmark = pytest.mark.gpu
+
+FEW, BAD = 40, 17   # drones of the small batch, the one with the input
+
+
+def _pair(w, plant):
+    """Results of the first FEW drones alone and within the whole batch."""
+    x0, cmds = w.x0.copy(), w.cmds.copy()
+    plant(x0, cmds)
+    w = dataclasses.replace(w, x0=x0, cmds=cmds)
+    run = (lambda v: _grads(_sim(v), v, 2)) if w.policy_hidden else (lambda v: _rollout_grads(v, 2))
+    few, many = run(W.subset(w, list(range(FEW)))), run(w)
+    return [(k, few[k][..., :FEW], many[k][..., :FEW]) for k in ("loss", "x", "g_cmds", "g_x0")]
+
+
+def _check(results):
+    for k, few, many in results:
+        few, many = few.double().cpu(), many.double().cpu()
+        assert torch.equal(torch.isfinite(few), torch.isfinite(many)), k
+        few, many = few.nan_to_num(0.0, 0.0, 0.0), many.nan_to_num(0.0, 0.0, 0.0)
+        per_drone = [v.reshape(-1, FEW).norm(dim=0) for v in (few - many, many)]
+        assert (per_drone[0] <= 1e-3 * per_drone[1].clamp_min(1e-12)).all(), k
+
+
+def _large():
+    return 128 * torch.cuda.get_device_properties(0).multi_processor_count + 70
+
+
+@pytest.mark.parametrize("value", [float("nan"), float("inf")])
+@pytest.mark.parametrize("where", ["angle", "rate", "command"])
+def test_yaw_does_not_reach_the_height(gpu_lib, where, value):
+    """The identified model's vertical acceleration does not depend on the yaw angle."""
+    w = dataclasses.replace(W.id_rollout_grad(seed=121, n_worlds=_large(), steps=3), gain=None, gain_index=None)
+
+    def plant(x0, cmds):
+        if where == "command":
+            cmds[:, 2, BAD] = value
+        else:
+            x0[5 if where == "angle" else 11, BAD] = value
+
+    results = _pair(w, plant)
+    _check(results)
+    x = dict((k, v) for k, v, _ in results)["x"]
+    assert torch.isfinite(x[2, BAD]) and torch.isfinite(x[8, BAD])

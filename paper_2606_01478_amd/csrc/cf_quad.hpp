@@ -266,7 +266,7 @@ __device__ __forceinline__ void q_fp_step_vjp(const QFpState& x, float rc, const
 // ---- attitude controller: axis j in lane j (yaw rate in lane 2), rotor j's
 // allocation in lane j, the commanded thrust in lane 3's command
 struct QPid {
-    float akp, aki, dta, rkp, rki, rkd, inv_dt, jc, dtr;   // lanes without the term: 0 (lane 2's akp: 1)
+    float akp, aki, dta, rkp, rki, rkd, inv_dt, jc, dtr;   // lanes without the term: 0
     float a0, a1, a2, a3, lo, hi, fr, k4, disc, k1w, vtx;
     float sp;                                      // 1, -1, 0, 0
 };
@@ -286,7 +286,7 @@ __device__ __forceinline__ QPid q_load_pid(const R& rec, int j, float dt, float 
     QPid C;
     const int j2 = j < 2 ? j : 1, j3 = j < 3 ? j : 2;
     const float m2 = j < 2 ? 1.f : 0.f, m3 = j < 3 ? 1.f : 0.f;
-    C.akp = j < 2 ? rec(P_ANG_KP + j2) : (j == 2 ? 1.f : 0.f);
+    C.akp = m2 * rec(P_ANG_KP + j2);
     C.aki = m2 * rec(P_ANG_KI + j2);
     C.dta = m2 * dt;
     C.rkp = m3 * rec(P_RATE_KP + j3);
@@ -326,7 +326,8 @@ __device__ __forceinline__ float q_pid(float q, float w, float n, float u, QPidS
     const float at = atan2_poly(y, x);
     const float ea = u - (j < 2 ? at : 0.f);
     c.ia = fma_(ea, C.dta, c.ia);
-    const float er = fma_(C.akp, ea, C.aki * c.ia) - w;
+    // (lane 2: the yaw-rate command itself; zero times an infinite one would be NaN)
+    const float er = (j < 2 ? fma_(C.akp, ea, C.aki * c.ia) : ea) - w;
     c.ir = fma_(er, C.dtr, c.ir);
     const float tq = C.jc * fma_(-(C.rkd * (w - c.wp)), C.inv_dt, fma_(C.rkp, er, C.rki * c.ir));
     c.wp = w;
@@ -350,7 +351,7 @@ __device__ __forceinline__ void q_pid_vjp(float q, const QPid& C, const QPidBack
     co.wp = C.rkd * al * C.inv_dt;
     *xw += (cb.wp - er) - co.wp;
     co.ia = fma_(C.aki, er, cb.ia);
-    const float ea = fma_(C.akp, er, co.ia * C.dta);
+    const float ea = j < 2 ? fma_(C.akp, er, co.ia * C.dta) : er;
     *ub += j == 3 ? wv : ea;
     // lane 0: adjoints of s1 and c1; lane 1: of s2
     const float i2 = rcp_hw(fma_(tr.y, tr.y, tr.x * tr.x));

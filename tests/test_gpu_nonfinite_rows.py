@@ -55,3 +55,38 @@ def test_yaw_does_not_reach_the_height(gpu_lib, where, value):
     _check(results)
     x = dict((k, v) for k, v, _ in results)["x"]
     assert torch.isfinite(x[2, BAD]) and torch.isfinite(x[8, BAD])
+
+
+@pytest.mark.parametrize("value", [float("inf"), float("-inf"), float("nan")])
+@pytest.mark.parametrize("row", [0, 1, 2, 3])
+def test_commands_that_saturate_the_attitude_controller(gpu_lib, row, value):
+    """The torque of an infinite angle or rate command saturates at the rotors' limits."""
+    w = W.gradient_goal(seed=122, n_worlds=_large(), steps=3)
+
+    def plant(x0, cmds):
+        cmds[1, row, BAD] = value
+
+    _check(_pair(w, plant))
+
+
+@pytest.mark.parametrize("k", [1, 4])
+def test_held_commands_that_saturate(gpu_lib, k):
+    """The same on held steps, bit for bit the one-lane kernel's."""
+    from gpu_helpers import dev
+
+    w = W.gradient_goal(seed=123, n_worlds=FEW, steps=1)
+    u = dev(w.cmds[0])
+    for d, (row, value) in enumerate([(2, "inf"), (2, "-inf"), (0, "inf"), (1, "-inf"), (3, "inf"), (2, "nan")]):
+        u[row, 3 * d] = float(value)
+    out = []
+    for wq in (0, 1):
+        sim, x = _sim(w), dev(w.x0)
+        sim.set_launch_config(workqueue=wq, tile=64)
+        sim.step_k(x, u, k)
+        torch.cuda.synchronize()
+        out.append(x)
+    assert torch.equal(torch.isfinite(out[0]), torch.isfinite(out[1]))
+    assert torch.equal(out[0].nan_to_num(0.0, 0.0, 0.0), out[1].nan_to_num(0.0, 0.0, 0.0))
+    # the yaw torque's sign is the command's: one pair of rotors speeds up, the other slows down
+    turn = (out[0][13] - out[0][14])[[0, 3]]
+    assert turn[0] * turn[1] < 0

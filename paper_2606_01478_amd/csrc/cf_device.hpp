@@ -1682,7 +1682,7 @@ __device__ __forceinline__ void id_step_structured_vjp(const float* x, const flo
         fx = __builtin_fmaf(P.st.p[s], fb[s], fx);
         fu = __builtin_fmaf(P.st.q[s], fb[s], fu);
     }
-    xb[12] = __builtin_fmaf(P.st.pf, yb[12], P.cf_m * fx);
+    xb[12] = P.direct ? 0.f : __builtin_fmaf(P.st.pf, yb[12], P.cf_m * fx);
     ub[3] += __builtin_fmaf(P.st.qf, yb[12], P.cf_m * fu);
 }
 

@@ -528,7 +528,7 @@ __device__ __forceinline__ void q_id_step_vjp(const QIdState& x, float u, const 
     // lane 3's t1..t4 are the specific thrusts' adjoints
     const float fx = qb<3>(fma_(P.p[0], t1, fma_(P.p[1], t2, fma_(P.p[2], t3, P.p[3] * t4))));
     const float fu = fma_(K.q[0], t1, fma_(K.q[1], t2, fma_(K.q[2], t3, K.q[3] * t4)));
-    out.f = fma_(P.pf, y.f, P.cf_m * fx);
+    out.f = P.direct ? 0.f : fma_(P.pf, y.f, P.cf_m * fx);
     *ub += j == 3 ? fma_(K.qf, y.f, P.cf_m * fu) : P.c3 * D;
 }
 

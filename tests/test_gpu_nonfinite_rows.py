@@ -90,3 +90,23 @@ def test_held_commands_that_saturate(gpu_lib, k):
     # the yaw torque's sign is the command's: one pair of rotors speeds up, the other slows down
     turn = (out[0][13] - out[0][14])[[0, 3]]
     assert turn[0] * turn[1] < 0
+
+
+@pytest.mark.parametrize("value", [float("nan"), float("inf")])
+@pytest.mark.parametrize("row", [3, 5, 11])
+def test_thrust_row_gradient_without_thrust_dynamics(gpu_lib, row, value):
+    """c_tau = 0: the start's thrust row has no influence, so its gradient is zero whatever
+    the drone's other gradients are."""
+    w = W.id_rollout_grad(seed=124, n_worlds=_large(), steps=3)
+    P = {k: v.copy() for k, v in w.params.items()}
+    P["c_tau"][:] = 0
+    w = dataclasses.replace(w, params=P, gain=None, gain_index=None)
+
+    def plant(x0, cmds):
+        x0[row, BAD] = value
+
+    results = _pair(w, plant)
+    _check(results)
+    for k, few, many in results:
+        if k == "g_x0":
+            assert (few[12] == 0).all() and (many[12] == 0).all()

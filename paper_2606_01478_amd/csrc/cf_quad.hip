@@ -429,8 +429,10 @@ __device__ __forceinline__ void q_outer_all(float b, const float* v, float* g) {
     }
 }
 
+// (units beyond the policy's H stay zero also where the input is infinite, which their zero
+// weights would make NaN)
 template <class Q, int U>
-__device__ __forceinline__ float q_mlp_forward(lds_float* m, const float* e, int j, float* h1, float* h2) {
+__device__ __forceinline__ float q_mlp_forward(lds_float* m, int H, const float* e, int j, float* h1, float* h2) {
     using M = QMlp<U>;
     float b1[U < 4 ? 4 : U], b2[U < 4 ? 4 : U];
 #pragma unroll
@@ -439,7 +441,8 @@ __device__ __forceinline__ float q_mlp_forward(lds_float* m, const float* e, int
     for (int r = 0; r < U; ++r) {
         float w[16];
         q_row<16>(m + M::W1 + (j * U + r) * M::S1, w);
-        h1[r] = tanhf(Q::dot13(w, e) + b1[r]);
+        const float h = tanhf(Q::dot13(w, e) + b1[r]);
+        h1[r] = j * U + r < H ? h : 0.f;
     }
 #pragma unroll
     for (int r = 0; r < U; ++r) h2[r] = tanhf(q_dot_all<U>(m + M::W2 + (j * U + r) * M::S2, h1, b2[r]));
@@ -503,7 +506,7 @@ __global__ __launch_bounds__(64) void k_quad_fwd(RollArgs a) {
             m.error(s, rp, rv, L.j, e);
             if constexpr (U > 0) {
                 float h1[U], h2[U];
-                o = q_mlp_forward<Q, U>(q_again(pol), e, L.j, h1, h2);
+                o = q_mlp_forward<Q, U>(q_again(pol), a.mlp_H, e, L.j, h1, h2);
             } else {
                 o = Q::dot13(g, e);
             }
@@ -563,7 +566,7 @@ __device__ __forceinline__ float q_command(const RollArgs& a, const Q& m, bool f
                                            float* h1, float* h2, float* o) {
     if (!fb && U == 0) return ubar;
     m.error(s, rp, rv, j, e);
-    if constexpr (U > 0) *o = q_mlp_forward<Q, U>(q_again(pol), e, j, h1, h2);
+    if constexpr (U > 0) *o = q_mlp_forward<Q, U>(q_again(pol), a.mlp_H, e, j, h1, h2);
     else *o = Q::dot13(g, e);
     if (EXT && a.squash) return fma_(a.act_s[j], tanhf(*o), ubar);
     return ubar + *o;

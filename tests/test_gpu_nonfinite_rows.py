@@ -110,3 +110,21 @@ def test_thrust_row_gradient_without_thrust_dynamics(gpu_lib, row, value):
     for k, few, many in results:
         if k == "g_x0":
             assert (few[12] == 0).all() and (many[12] == 0).all()
+
+
+@pytest.mark.parametrize("hidden", [1, 8, 9, 13, 31])
+@pytest.mark.parametrize("row", [0, 12])
+@pytest.mark.parametrize("steps", [1, 3])
+def test_policies_saturate_where_their_input_is_infinite(gpu_lib, hidden, row, steps):
+    """tanh of an infinite activation is one, so the commands stay finite; widths that a
+    quad's lanes pad with units of zero weights among them. (For one step: the compensated
+    sums make an infinite position, or the velocity under an infinite thrust, NaN.)"""
+    w = W.id_rollout_grad_mlp(seed=125, n_worlds=_large(), steps=steps, hidden=hidden, out_scale=0.05)
+
+    def plant(x0, cmds):
+        x0[row, BAD] = np.inf
+
+    results = _pair(w, plant)
+    _check(results)
+    x = dict((k, v) for k, v, _ in results)["x"]
+    assert steps > 1 or torch.isfinite(x[3:6, BAD]).all()
